@@ -191,3 +191,36 @@ def test_sheared_touch_lists_bit_exact():
     assert np.any(np.floor(off[0, :, 2] + o[0, 2] - 1) < lat.nz) and np.any(off[0, :, 2] + o[0, 2] + 2 >= lat.nz)
     assert np.array_equal(tptr, ptr_r)
     assert np.array_equal(touch, vid_r)
+
+
+@pytest.mark.parametrize("shape,kernel,cells_at,pull", [
+    ((16, 12, 16), 2, 1, 2e-3),     # the hat; two tiles along z
+    ((24, 16, 8), 4, 1, 2e-3),      # one tile along z: both images in it
+    ((24, 17, 24), 4, 7, 2e-3),     # tiles of more than 512 entries (staged in chunks), ragged y
+    ((24, 20, 24), 4, 1, 0.5),      # vertex forces above 2^-9 (full-range conversion)
+])
+def test_lattice_pass_forms(shape, kernel, cells_at, pull):
+    """Two steps of every form of the sheared lattice pass, cells across z = nz
+    (their origins an image further along z) against the FP64 oracle."""
+    U = 0.021
+    lat = Lattice(*shape, tau=0.9, lees_edwards_u=U, ibm_kernel=kernel)
+    rest64, tri = rbc_mesh()
+    rng = np.random.default_rng(77)
+    n = cells_at
+    cen = np.array([lat.nx * 0.4, lat.ny * 0.5, 2 * lat.nz - 1.2]) + rng.uniform(-0.3, 0.3, (n, 3))
+    rots = np.stack([small_rotation(rng, 10.0) for _ in range(n)])
+    cells = jitter_cells(rng, place_cells(rest64, cen, rots, np.repeat(K_REF[None], n, 0),
+                                          traction=np.repeat([[pull, 0, 0]], n, 0)), 0.03)
+    g0 = random_shifted_populations(rng, lat, 1e-3)
+    sim = _sim(lat, cells)
+    sim.write_populations(g0)
+    sim.step(2)
+    sim.sync()
+    m = _oracle(lat, rest64, tri, cells, U)
+    f, X = lattice.unshift(g0), cells.positions64()
+    for t in range(2):
+        f, X, info = step.step(m, f, X, t)
+    e_g = relerr(sim.read_populations(), lattice.shifted(f))
+    e_u = relerr(sim.read_vertex_velocity(), info["U"])
+    print(shape, kernel, cells_at, pull, "populations", e_g, "velocity", e_u, flush=True)
+    assert e_g <= 2 * TOL_STEP and e_u <= 2 * TOL_STEP
