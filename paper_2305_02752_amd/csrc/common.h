@@ -37,6 +37,15 @@ constexpr float kFix32Max = 2147483520.0f;
 // Distinct interior viscosity ratios (classes) one lattice may hold at once.
 constexpr int kVisClasses = 8;
 
+// Work-group barrier for data in LDS alone.  __syncthreads also waits for
+// every global load and store in flight: loads requested ahead of their use
+// would be waited for at the next barrier, and stores for nothing.
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 [[maybe_unused]] static __device__ __noinline__ void fix_add3_wide(long long* a0, long long* a1,
                                                                    long long* a2, float x, float y,
                                                                    float z) {

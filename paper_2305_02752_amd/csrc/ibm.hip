@@ -314,9 +314,8 @@ __host__ __device__ inline int tile_grid(const Lattice& L) { return ((L.ntiles +
 // Sorted-entry form of the two immersed-boundary phases.
 //
 // The (vertex, tile) entries of a tile are staged in LDS as compact records:
-// per axis the tile-local nodes of the stencil positions that fall inside
-// the tile, in stencil order, with their stencil index; the fractional
-// position; the vertex force.  The records are ordered by the shape of
+// per axis the run of stencil positions that fall inside the tile; the
+// fractional position; the vertex force.  The records are ordered by the shape of
 // their in-tile box (nodes per axis), so the lanes of a wave share their
 // loop bounds, and each lane walks only its entry's in-tile nodes with
 // statically indexed registers.  All four stencil weights of an axis come
@@ -340,16 +339,27 @@ __host__ __device__ inline int tile_grid(const Lattice& L) { return ((L.ntiles +
 // image's velocity.  Its forces accumulate as 2^-40 fixed-point int64.
 namespace srt {
 
-constexpr int kStage = 512;   // records staged at once (two per thread)
+// Records staged at once.  With 32 bytes each the work-group's LDS allows six
+// per CU; 768 records (five per CU) took 2.40 ms for 2.24 on 256 x 256 x 512
+// sites with 18,600 cells (475 entries per tile), 400 (eight) 2.26.
+constexpr int kThreads = 256;
+constexpr int kStage = 512;
+constexpr int kPerThread = kStage / kThreads;
 constexpr int kKeys = 64;     // box shapes: 1..4 in-tile nodes on each axis
+// LDS pitch of the node arrays.  Clipped boxes start at few distinct nodes, so
+// with rows of 8 and planes of 64 the lanes of a wave pile up on few banks (8.3
+// cycles per LDS access, counted): counting lanes per bank over the entries of
+// a dense suspension, 7.2 to 8.0 per atomic and 3.5 to 3.9 per read with
+// pitches 8 and 64, 5.1 and 2.3 with 9 and 77.
+constexpr int kRow = 9, kPlane = 77, kNodes = 8 * kPlane;
+__device__ __forceinline__ int node_at(int i) { return (i >> 6) * kPlane + ((i >> 3) & 7) * kRow + (i & 7); }
 
 template <bool LE>
 struct Smem {
   // spread accumulator: int32 at the tile's scale (sheared images: 2^-40 int64)
-  typename std::conditional<LE, long long, int>::type acc[3][512];
-  int4 geo[kStage];         // axis words x, y, z; entry code (vertex * 32 + slot)
-  float4 fr[kStage];        // fractions x, y, z; force x
-  float2 fyz[kStage];       // force y, z
+  typename std::conditional<LE, long long, int>::type acc[3][kNodes];
+  float4 pos[kStage];       // fractions x, y, z; axis runs (bits)
+  float4 force[kStage];     // force x, y, z; entry code (vertex * 32 + slot, bits)
   int cnt[kKeys];           // records per box shape, then the first record of each shape
   unsigned fmax;            // largest force component magnitude (float bits)
   int fsum;                 // sum of the entries' largest components, in units of fmax 2^-bexp
@@ -376,36 +386,23 @@ struct Smem {
   }
 };
 
-// In-tile stencil list along one axis: of the K positions base + k (wrapped
-// on a periodic axis, dropped past a wall), those in [t0, t0 + 8) in
-// stencil order; slot s holds (node - t0) | k << 3 at bits 5s..5s+4, the
-// count sits at bits 20..22.  A stencil that does not run over the end of
-// the lattice meets the tile in one contiguous run of positions.
+// In-tile run along one axis: the K positions base + k (wrapped on a periodic
+// axis, dropped past a wall) meet the tile's nodes [t0, t0 + 8) in one run of
+// consecutive stencil indices and nodes.  Only on a periodic axis of up to
+// kSmall nodes can the first tile hold nodes on both sides of the seam; the
+// run is then all K positions from p0 on, see node().  Bits 0..2: first node
+// - t0, 3..4: its stencil index, 5..7: count.
+constexpr int kSmall = 10;
 template <int K>
-__device__ __forceinline__ unsigned axis_word(int base, int n, int wall, int t0) {
-  const int p0 = wall ? base : wrap(base, n);
-  if (wall || p0 + K <= n) {
-    const int lo = max(max(p0, t0), 0), hi = min(min(p0 + K, t0 + kTile), n);
-    const int c = max(hi - lo, 0);
-    const unsigned first = (unsigned)((lo - t0) | ((lo - p0) << 3));
-    unsigned w = 0;
-#pragma unroll
-    for (int s = 0; s < K; ++s)   // slot s: node and stencil index both one past slot s - 1
-      if (s < c) w |= (first + (unsigned)(s | (s << 3))) << (5 * s);
-    return w | ((unsigned)c << 20);
+__device__ __forceinline__ unsigned axis_run(int base, int n, int wall, int t0) {
+  int p0 = wall ? base : wrap(base, n);
+  if (!wall && p0 + K > n && t0 == 0) {
+    if (p0 < kTile) return (unsigned)(p0 | (K << 5));
+    p0 -= n;
   }
-  unsigned w = 0;
-  int c = 0;
-#pragma unroll
-  for (int k = 0; k < K; ++k) {
-    int q = p0 + k;
-    q = q >= n ? q - n : q;   // q < n + K <= 2n (sides are at least 4)
-    if (q >= t0 && q < t0 + kTile) {
-      w |= (unsigned)((q - t0) | (k << 3)) << (5 * c);
-      ++c;
-    }
-  }
-  return w | ((unsigned)c << 20);
+  const int lo = max(max(p0, t0), 0), hi = min(min(p0 + K, t0 + kTile), n);
+  const int c = max(hi - lo, 0);
+  return c ? (unsigned)((lo - t0) | ((lo - p0) << 3) | (c << 5)) : 0u;
 }
 
 template <int K>
@@ -426,24 +423,37 @@ __device__ __forceinline__ void weights(float f, float (&W)[4]) {
 }
 
 struct Axis {
-  int n;
-  int l[4];
+  int n, l0;
   float w[4];
 };
 
-template <int K>
-__device__ __forceinline__ void decode(unsigned word, float f, Axis& A) {
+// Run and weights of an axis of n nodes: w[s] is the weight of the run's s-th
+// node.  SMALL (some axis of the lattice has up to kSmall nodes): a run across
+// the seam wraps, and its nodes in the second tile weigh nothing here.
+template <int K, bool SMALL>
+__device__ __forceinline__ void decode(unsigned run, float f, int n, Axis& A) {
   float W[4];
   weights<K>(f, W);
-  A.n = (int)((word >> 20) & 7u);
+  A.l0 = (int)(run & 7u);
+  A.n = (int)((run >> 5) & 7u);
+  const bool k1 = run & 8u, k2 = run & 16u;   // shift by the first stencil index
+  const float a = k1 ? W[1] : W[0], b = k1 ? W[2] : W[1], c = k1 ? W[3] : W[2], d = W[3];
+  A.w[0] = k2 ? c : a;
+  A.w[1] = k2 ? d : b;
+  A.w[2] = c;
+  A.w[3] = d;
+  if (SMALL) {
 #pragma unroll
-  for (int s = 0; s < 4; ++s) {
-    const unsigned q = (word >> (5 * s)) & 31u;
-    const unsigned k = q >> 3;
-    A.l[s] = (int)(q & 7u);
-    const float lo = (k & 1u) ? W[1] : W[0], hi = (k & 1u) ? W[3] : W[2];
-    A.w[s] = (k & 2u) ? hi : lo;
+    for (int s = 0; s < 4; ++s)
+      if (A.l0 + s >= kTile && A.l0 + s < n) A.w[s] = 0.f;
   }
+}
+
+// Tile-local node s of a run on an axis of n nodes.
+template <bool SMALL>
+__device__ __forceinline__ int node(int l0, int s, int n) {
+  const int l = l0 + s;
+  return SMALL ? min(l >= n ? l - n : l, kTile - 1) : l;
 }
 
 // Largest weight one entry can put on one node: the product over the axes
@@ -515,7 +525,7 @@ __device__ __forceinline__ float entry_fmax(const Cells& C, const Bins& B, int t
 // again for the sum.  Ends synchronised.
 constexpr int kBoundKeep = (int)(sizeof(float4) * kStage / sizeof(float));
 __device__ __forceinline__ void force_bound(const Cells& C, const Bins& B, int t, int ne, Smem<false>& S) {
-  float* kept = reinterpret_cast<float*>(S.fr);
+  float* kept = reinterpret_cast<float*>(S.pos);
   const bool keep = ne <= kBoundKeep;
   float m = 0.f;
   for (int i = threadIdx.x; i < ne; i += blockDim.x) {
@@ -525,14 +535,25 @@ __device__ __forceinline__ void force_bound(const Cells& C, const Bins& B, int t
   }
   m = wave_max(m);
   if ((threadIdx.x & (kWave - 1)) == 0) atomicMax(&S.fmax, __float_as_uint(m));
-  __syncthreads();
+  lds_barrier();
   const float fmx = __uint_as_float(S.fmax), rf = __builtin_amdgcn_rcpf(fmx);
   int u = 0;
   for (int i = threadIdx.x; i < ne; i += blockDim.x)
     u += bound_units(keep ? kept[i] : entry_fmax(C, B, t, i), fmx, rf, B.bexp);
   u = wave_sum(u);
   if ((threadIdx.x & (kWave - 1)) == 0) atomicAdd(&S.fsum, u);
-  __syncthreads();
+  lds_barrier();
+}
+
+// Place of a box shape (nodes per axis less one) in the order of the
+// records: z by z, alternately up and down in y and x, so that neighbouring
+// shapes differ by one node on one axis.  A wave holds records of about ten
+// shapes and loops to the largest count of each axis: 10% fewer nodes than
+// counting up on every axis.
+__device__ __forceinline__ int shape_key(int x, int y, int z) {
+  y ^= z & 1 ? 3 : 0;
+  const int r = z * 4 + y;
+  return r * 4 + (x ^ (r & 1 ? 3 : 0));
 }
 
 // Chunks of a list longer than kStage: a first one of 1..kStage entries,
@@ -540,7 +561,7 @@ __device__ __forceinline__ void force_bound(const Cells& C, const Bins& B, int t
 // one, and it is still staged when the interpolation starts.
 __device__ __forceinline__ int first_chunk(int ne) { return ne - (ne - 1) / kStage * kStage; }
 
-// Stage entries [e0, e0 + m) of tile t (m <= kStage, two per thread) as
+// Stage entries [e0, e0 + m) of tile t (m <= kStage) as
 // records ordered by box shape; with_force also stages the forces, and with
 // bound as well the force bound of these entries (S.fmax, S.fsum: the whole
 // tile's when they are all staged at once).  Ends synchronised.
@@ -549,22 +570,22 @@ __device__ __forceinline__ void stage(const Cells& C, const Mesh& M, const Latti
                              int x0, int y0, int z0, int e0, int m, bool with_force, bool bound,
                              Smem<LE>& S) {
   for (int i = threadIdx.x; i < kKeys; i += blockDim.x) S.cnt[i] = 0;
-  __syncthreads();
-  int4 g[2];
-  float4 fr[2];
-  float2 fyz[2];
-  int key[2], rank[2], image[2] = {0, 0};
-  float fm[2] = {0.f, 0.f};
+  lds_barrier();
+  constexpr int R = kPerThread;
+  float4 pos[R], force[R];
+  int key[R], rank[R], image[R];
+  float fmax = 0.f, fm[R];
   const int b = K == 4 ? -1 : 0;
   const float rnv = __builtin_amdgcn_rcpf((float)M.nv);
 #pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int i = (int)threadIdx.x + h * (int)blockDim.x;
+  for (int h = 0; h < R; ++h) {
+    const int i = (int)threadIdx.x + h * kThreads;
     key[h] = -1;
     rank[h] = 0;
-    g[h] = make_int4(0, 0, 0, 0);
-    fr[h] = make_float4(0.f, 0.f, 0.f, 0.f);
-    fyz[h] = make_float2(0.f, 0.f);
+    image[h] = 0;
+    fm[h] = 0.f;
+    pos[h] = make_float4(0.f, 0.f, 0.f, 0.f);
+    force[h] = make_float4(0.f, 0.f, 0.f, 0.f);
     if (i < m) {
       const int code = B.touch[(int64_t)t * B.cap + e0 + i];
       const int v = code >> 5, c = div_small(v, M.nv, rnv);
@@ -572,38 +593,39 @@ __device__ __forceinline__ void stage(const Cells& C, const Mesh& M, const Latti
       float ox = o[0];
       const float oy = o[1], oz = o[2];
       const float fy = floorf(oy), fz = floorf(oz);
+      const int bz = C.origin[3 * c + 2] + (int)fz + b;
+      const unsigned rz = axis_run<K>(bz, L.nz, L.bc[2] == 1, z0);
       if (LE) {   // the image of the first in-tile z node is that of all of them
-        const int bz = C.origin[3 * c + 2] + (int)fz + b;
-        image[h] = floor_div(bz + (int)((axis_word<K>(bz, L.nz, 0, z0) >> 3) & 3u), L.nz);
+        image[h] = floor_div(bz + (int)((rz >> 3) & 3u), L.nz);
         ox = fmaf(-(float)image[h], L.le_delta, ox);
       }
       const float fx = floorf(ox);
-      const unsigned wx = axis_word<K>(C.origin[3 * c] + (int)fx + b, L.nx, L.bc[0] == 1, x0);
-      const unsigned wy = axis_word<K>(C.origin[3 * c + 1] + (int)fy + b, L.ny, L.bc[1] == 1, y0);
-      const unsigned wz = axis_word<K>(C.origin[3 * c + 2] + (int)fz + b, L.nz, L.bc[2] == 1, z0);
-      g[h] = make_int4((int)wx, (int)wy, (int)wz, code);
-      fr[h] = make_float4(ox - fx, oy - fy, oz - fz, 0.f);
+      const unsigned rx = axis_run<K>(C.origin[3 * c] + (int)fx + b, L.nx, L.bc[0] == 1, x0);
+      const unsigned ry = axis_run<K>(C.origin[3 * c + 1] + (int)fy + b, L.ny, L.bc[1] == 1, y0);
+      pos[h] = make_float4(ox - fx, oy - fy, oz - fz, __uint_as_float(rx | (ry << 8) | (rz << 16)));
+      force[h].w = __int_as_float(code);
       if (with_force) {
         const float* fv = C.force + (int64_t)v * 3;
-        fr[h].w = fv[0];
-        fyz[h] = make_float2(fv[1], fv[2]);
+        force[h].x = fv[0];
+        force[h].y = fv[1];
+        force[h].z = fv[2];
         fm[h] = fmaxf(fabsf(fv[0]), fmaxf(fabsf(fv[1]), fabsf(fv[2])));
+        fmax = fmaxf(fmax, fm[h]);
       }
-      const int nx = (int)((wx >> 20) & 7u), ny = (int)((wy >> 20) & 7u), nz = (int)((wz >> 20) & 7u);
-      key[h] = ((max(nz, 1) - 1) * 4 + (max(ny, 1) - 1)) * 4 + (max(nx, 1) - 1);
+      key[h] = shape_key(max((int)(rx >> 5), 1) - 1, max((int)(ry >> 5), 1) - 1, max((int)(rz >> 5), 1) - 1);
       rank[h] = atomicAdd(&S.cnt[key[h]], 1);
     }
   }
   if (bound) {
-    const float w = wave_max(fmaxf(fm[0], fm[1]));
+    const float w = wave_max(fmax);
     if ((threadIdx.x & (kWave - 1)) == 0) atomicMax(&S.fmax, __float_as_uint(w));
   }
-  __syncthreads();
+  lds_barrier();
   if (bound) {   // S.fmax is complete: the bound sum (read after the final barrier)
     const float fmx = __uint_as_float(S.fmax), rf = __builtin_amdgcn_rcpf(fmx);
     int u = 0;
 #pragma unroll
-    for (int h = 0; h < 2; ++h)
+    for (int h = 0; h < R; ++h)
       if (key[h] >= 0) u += bound_units(fm[h], fmx, rf, B.bexp);
     u = wave_sum(u);
     if ((threadIdx.x & (kWave - 1)) == 0) atomicAdd(&S.fsum, u);
@@ -618,17 +640,16 @@ __device__ __forceinline__ void stage(const Cells& C, const Mesh& M, const Latti
     }
     S.cnt[threadIdx.x] = v - own;
   }
-  __syncthreads();
+  lds_barrier();
 #pragma unroll
-  for (int h = 0; h < 2; ++h) {
+  for (int h = 0; h < R; ++h) {
     if (key[h] < 0) continue;
     const int p = S.cnt[key[h]] + rank[h];
-    S.geo[p] = g[h];
-    S.fr[p] = fr[h];
-    S.fyz[p] = fyz[h];
+    S.pos[p] = pos[h];
+    S.force[p] = force[h];
     if (LE) S.image[p] = image[h];
   }
-  __syncthreads();
+  lds_barrier();
 }
 
 // Spread the m staged records into S.acc at the scale 2^kexp.  Node
@@ -641,8 +662,8 @@ __device__ __forceinline__ void stage(const Cells& C, const Mesh& M, const Latti
 // and more take the full-range conversion (WIDE), a truncation as well, so
 // which of the two an entry takes never changes an integer.
 constexpr int kRoundAbove = 1024;
-template <int K, bool RN, bool WIDE, bool LE>
-__device__ __forceinline__ void spread_entries(int m, float scale, Smem<LE>& S) {
+template <int K, bool RN, bool WIDE, bool SMALL, bool LE>
+__device__ __forceinline__ void spread_entries(int m, const Lattice& L, float scale, Smem<LE>& S) {
   auto add = [&](int comp, int li, float q) {
     if (LE) {
       const long long n = WIDE ? (long long)q : (long long)(int)q;
@@ -652,14 +673,13 @@ __device__ __forceinline__ void spread_entries(int m, float scale, Smem<LE>& S) 
     }
   };
   for (int i = threadIdx.x; i < m; i += blockDim.x) {
-    const int4 g = S.geo[i];
-    const float4 fr = S.fr[i];
-    const float2 fyz = S.fyz[i];
+    const float4 pos = S.pos[i], force = S.force[i];
+    const unsigned run = __float_as_uint(pos.w);
     Axis X, Y, Z;
-    decode<K>((unsigned)g.x, fr.x, X);
-    decode<K>((unsigned)g.y, fr.y, Y);
-    decode<K>((unsigned)g.z, fr.z, Z);
-    const float fx = fr.w * scale, fy = fyz.x * scale, fz = fyz.y * scale;
+    decode<K, SMALL>(run, pos.x, L.nx, X);
+    decode<K, SMALL>(run >> 8, pos.y, L.ny, Y);
+    decode<K, SMALL>(run >> 16, pos.z, L.nz, Z);
+    const float fx = force.x * scale, fy = force.y * scale, fz = force.z * scale;
     float gx[K], gy[K], gz[K];
 #pragma unroll
     for (int s = 0; s < K; ++s) {
@@ -674,11 +694,11 @@ __device__ __forceinline__ void spread_entries(int m, float scale, Smem<LE>& S) 
       for (int iy = 0; iy < K; ++iy) {
         if (iy >= Y.n) continue;
         const float wzy = Z.w[iz] * Y.w[iy];
-        const int row = Z.l[iz] * (kTile * kTile) + Y.l[iy] * kTile;
+        const int row = node<SMALL>(Z.l0, iz, L.nz) * kPlane + node<SMALL>(Y.l0, iy, L.ny) * kRow;
 #pragma unroll
         for (int ix = 0; ix < K; ++ix) {
           if (ix >= X.n) continue;
-          const int li = row + X.l[ix];
+          const int li = row + node<SMALL>(X.l0, ix, L.nx);
           add(0, li, wzy * gx[ix]);
           add(1, li, wzy * gy[ix]);
           add(2, li, wzy * gz[ix]);
@@ -688,17 +708,19 @@ __device__ __forceinline__ void spread_entries(int m, float scale, Smem<LE>& S) 
   }
 }
 
-template <int K, bool LE>
-__device__ __forceinline__ void spread(int m, int ne, int kexp, Smem<LE>& S) {
+template <int K, bool SMALL, bool LE>
+__device__ __forceinline__ void spread(int m, const Lattice& L, int ne, int kexp, Smem<LE>& S) {
   if constexpr (LE) {
-    bool wide = false;   // the wave's choice: any of its forces of 2^-9 or more
-    for (int i = threadIdx.x; i < m; i += blockDim.x)
-      wide = wide || !(fmaxf(fabsf(S.fr[i].w), fmaxf(fabsf(S.fyz[i].x), fabsf(S.fyz[i].y))) * kFixScaleF < kFix32Max);
-    if (__any(wide)) spread_entries<K, false, true>(m, kFixScaleF, S);
-    else spread_entries<K, false, false>(m, kFixScaleF, S);
+    bool wide = false;   // the wave's choice: any of its forces
+    for (int i = threadIdx.x; i < m; i += kThreads) {
+      const float4 f = S.force[i];
+      wide = wide || !(fmaxf(fabsf(f.x), fmaxf(fabsf(f.y), fabsf(f.z))) * kFixScaleF < kFix32Max);
+    }
+    if (__any(wide)) spread_entries<K, false, true, SMALL>(m, L, kFixScaleF, S);
+    else spread_entries<K, false, false, SMALL>(m, L, kFixScaleF, S);
   } else {
-    if (ne > kRoundAbove) spread_entries<K, true, false>(m, ldexpf(1.f, kexp), S);
-    else spread_entries<K, false, false>(m, ldexpf(1.f, kexp), S);
+    if (ne > kRoundAbove) spread_entries<K, true, false, SMALL>(m, L, ldexpf(1.f, kexp), S);
+    else spread_entries<K, false, false, SMALL>(m, L, ldexpf(1.f, kexp), S);
   }
 }
 
@@ -706,26 +728,22 @@ __device__ __forceinline__ void spread(int m, int ne, int kexp, Smem<LE>& S) {
 // held in S.acc (float bits), summed over the in-tile nodes in stencil
 // order, into the records' partial-sum slots.
 // With sheared images every node carries its image's velocity.
-template <int K, bool LE>
-__device__ __forceinline__ void interp(int m, const Smem<LE>& S, float le_u, int64_t stride,
+template <int K, bool SMALL, bool LE>
+__device__ __forceinline__ void interp(int m, const Lattice& L, const Smem<LE>& S, int64_t stride,
                                        float4* __restrict__ partial) {
   for (int i = threadIdx.x; i < m; i += blockDim.x) {
-    const int4 g = S.geo[i];
-    const float4 fr = S.fr[i];
+    const float4 pos = S.pos[i];
+    const unsigned run = __float_as_uint(pos.w);
     Axis X, Y, Z;
-    decode<K>((unsigned)g.x, fr.x, X);
-    decode<K>((unsigned)g.y, fr.y, Y);
-    decode<K>((unsigned)g.z, fr.z, Z);
-    // x slots past the entry's count read its first node with weight zero,
-    // so a row's reads carry no branch and issue together
+    decode<K, SMALL>(run, pos.x, L.nx, X);
+    decode<K, SMALL>(run >> 8, pos.y, L.ny, Y);
+    decode<K, SMALL>(run >> 16, pos.z, L.nz, Z);
+    // x slots past the entry's count carry weight zero and read on along the
+    // row, so a row's reads have no branch and issue together
     float wx[K];
-    int lx[K];
 #pragma unroll
-    for (int s = 0; s < K; ++s) {
-      wx[s] = s < X.n ? X.w[s] : 0.f;
-      lx[s] = s < X.n ? X.l[s] : X.l[0];
-    }
-    const float shift = LE ? (float)S.image[i] * le_u : 0.f;
+    for (int s = 0; s < K; ++s) wx[s] = s < X.n ? X.w[s] : 0.f;
+    const float shift = LE ? (float)S.image[i] * L.le_u : 0.f;
     float sx = 0.f, sy = 0.f, sz = 0.f;
 #pragma unroll
     for (int iz = 0; iz < K; ++iz) {
@@ -734,11 +752,11 @@ __device__ __forceinline__ void interp(int m, const Smem<LE>& S, float le_u, int
       for (int iy = 0; iy < K; ++iy) {
         if (iy >= Y.n) continue;
         const float wzy = Z.w[iz] * Y.w[iy];
-        const int row = Z.l[iz] * (kTile * kTile) + Y.l[iy] * kTile;
+        const int row = node<SMALL>(Z.l0, iz, L.nz) * kPlane + node<SMALL>(Y.l0, iy, L.ny) * kRow;
         float rx = 0.f, ry = 0.f, rz = 0.f;
 #pragma unroll
         for (int ix = 0; ix < K; ++ix) {
-          const float3 u = S.get_u(row + lx[ix]);
+          const float3 u = S.get_u(row + node<SMALL>(X.l0, ix, L.nx));
           rx += wx[ix] * (LE ? u.x + shift : u.x);
           ry += wx[ix] * u.y;
           rz += wx[ix] * u.z;
@@ -748,7 +766,8 @@ __device__ __forceinline__ void interp(int m, const Smem<LE>& S, float le_u, int
         sz += wzy * rz;
       }
     }
-    const int v = g.w >> 5, j = g.w & 31;
+    const int code = __float_as_int(S.force[i].w);
+    const int v = code >> 5, j = code & 31;
     partial[(int64_t)j * stride + v] = make_float4(sx, sy, sz, 0.f);
   }
 }
@@ -767,6 +786,12 @@ __device__ __forceinline__ void interp(int m, const Smem<LE>& S, float le_u, int
 //     inside a cell and relaxes at L.omega_in of its highest set bit (the
 //     most viscous class containing it), and its byte is cleared;
 //  3. interpolate u to the staged entries into their partial-sum slots.
+// Bound by the node loops of 1 and 3 (LDS atomics and reads, then the vector
+// instructions around them), not by the populations' traffic: with the padded
+// pitch, the up-and-down record order, 32-byte records and barriers that wait
+// for LDS only, 2.77 -> 2.24 ms on 256 x 256 x 512 sites with 18,600 cells
+// (the populations alone take 0.86 at copy rate), 64 -> 55 us on a walled
+// 128 x 64 x 64 with 220, 379 -> 224 us with sheared images on 128^3 with 1160.
 // Tiles with more entries than the LDS stages at once take them in chunks
 // (the scale then comes from a first pass over all their forces, and the
 // interpolation stages again every chunk but the last).
@@ -786,7 +811,7 @@ __device__ __forceinline__ void tile_step_sorted_body(CT C, MT M, LT L, BT B,
   if (t < 0) return;
   int x0, y0, z0;
   tile_origin(L, t, x0, y0, z0);
-  for (int i = threadIdx.x; i < kTile * kTile * kTile; i += blockDim.x) {
+  for (int i = threadIdx.x; i < srt::kNodes; i += blockDim.x) {
     S.acc[0][i] = 0;
     S.acc[1][i] = 0;
     S.acc[2][i] = 0;
@@ -797,7 +822,10 @@ __device__ __forceinline__ void tile_step_sorted_body(CT C, MT M, LT L, BT B,
   }
   const int ne = C.n > 0 ? min(B.touch_cnt[t], B.cap) : 0;
   __syncthreads();
+  // every thread has read the count: leave it zero for the next binning
+  if (ne > 0 && threadIdx.x == 0) B.touch_cnt[t] = 0;
   int kexp = 0;
+  const bool small = min(L.nx, min(L.ny, L.nz)) <= srt::kSmall;
   if (ne > 0) {
     // the scale must cover every chunk (the int64 sums need none)
     const bool bound = !LE && ne <= srt::kStage;
@@ -807,7 +835,8 @@ __device__ __forceinline__ void tile_step_sorted_body(CT C, MT M, LT L, BT B,
       srt::stage<K, LE>(C, M, L, B, t, x0, y0, z0, e0, m, true, bound, S);
       if (!LE && e0 == 0)
         kexp = srt::fix_exponent(S.fsum, __uint_as_float(S.fmax), srt::max_node_weight(L), B.bexp);
-      srt::spread<K, LE>(m, ne, kexp, S);
+      if (small) srt::spread<K, true>(m, L, ne, kexp, S);
+      else srt::spread<K, false>(m, L, ne, kexp, S);
       __syncthreads();
     }
   }
@@ -819,9 +848,9 @@ __device__ __forceinline__ void tile_step_sorted_body(CT C, MT M, LT L, BT B,
   // indices stay below 2^30, so they serve as 32-bit element offsets.
   const unsigned py = (unsigned)L.tx << 9, pz = py * (unsigned)L.ty;
   for (int i = threadIdx.x; i < kTile * kTile * kTile; i += blockDim.x) {
-    const int x = x0 + (i & 7), y = y0 + ((i >> 3) & 7), z = z0 + (i >> 6);
+    const int x = x0 + (i & 7), y = y0 + ((i >> 3) & 7), z = z0 + (i >> 6), li = srt::node_at(i);
     if (x >= L.nx || y >= L.ny || z >= L.nz) {
-      S.put_u(i, 0.f, 0.f, 0.f);
+      S.put_u(li, 0.f, 0.f, 0.f);
       continue;
     }
     const int xm = x == 0 ? L.nx - 1 : x - 1, xp = x == L.nx - 1 ? 0 : x + 1;
@@ -861,7 +890,7 @@ __device__ __forceinline__ void tile_step_sorted_body(CT C, MT M, LT L, BT B,
     }
     // each thread reads and then overwrites only its own nodes' slots
     auto sum = [&](int d) {
-      return LE ? (float)((double)S.acc[d][i] * kFixInv) : ldexpf((float)S.acc[d][i], -kexp);
+      return LE ? (float)((double)S.acc[d][li] * kFixInv) : ldexpf((float)S.acc[d][li], -kexp);
     };
     const float fx = L.g[0] + sum(0), fy = L.g[1] + sum(1), fz = L.g[2] + sum(2);
     float rho, ux, uy, uz;
@@ -875,7 +904,7 @@ __device__ __forceinline__ void tile_step_sorted_body(CT C, MT M, LT L, BT B,
       }
     }
     lbm::collide(g, fx, fy, fz, omega, rho, ux, uy, uz);
-    S.put_u(i, ux, uy, uz);
+    S.put_u(li, ux, uy, uz);
     if (fields) {
       macro[h] = make_float4(ux, uy, uz, rho);
       F[h] = fx;
@@ -896,22 +925,24 @@ __device__ __forceinline__ void tile_step_sorted_body(CT C, MT M, LT L, BT B,
     }
   }
   if (ne == 0) return;
-  __syncthreads();
+  lds_barrier();   // the velocities; the populations' stores need no wait
   const int64_t stride = (int64_t)C.n * M.nv;
+  auto interp = [&](int m) {
+    if (small) srt::interp<K, true>(m, L, S, stride, partial);
+    else srt::interp<K, false>(m, L, S, stride, partial);
+  };
   if (ne <= srt::kStage) {
-    srt::interp<K, LE>(ne, S, L.le_u, stride, partial);
+    interp(ne);
   } else {
     // the last chunk of the spread is still staged; the others stage again
-    srt::interp<K, LE>(srt::kStage, S, L.le_u, stride, partial);
-    __syncthreads();
+    interp(srt::kStage);
+    lds_barrier();
     for (int e0 = 0, m = srt::first_chunk(ne); e0 < ne - srt::kStage; e0 += m, m = srt::kStage) {
       srt::stage<K, LE>(C, M, L, B, t, x0, y0, z0, e0, m, false, false, S);
-      srt::interp<K, LE>(m, S, L.le_u, stride, partial);
-      __syncthreads();
+      interp(m);
+      lds_barrier();
     }
   }
-  __syncthreads();   // every thread has read the count: leave it zero for the next binning
-  if (threadIdx.x == 0) B.touch_cnt[t] = 0;
 }
 
 template <int K, bool W>
@@ -929,7 +960,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void k
 
 // Sheared images.  The entry-parallel form below tests every axis slot at
 // every node and keeps its entries unsorted: 379 us on 128^3 with 1160 cells,
-// this one 259 us.  Bound by the 64-bit LDS atomics of the spread.
+// this one 224 us.  Bound by the 64-bit LDS atomics of the spread.
 template <int K>
 __global__ __launch_bounds__(256) void k_tile_step_sorted_le(Cells C, Mesh M, Lattice L, Bins B,
                                                              const float* __restrict__ gin,

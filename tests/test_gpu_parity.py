@@ -489,3 +489,32 @@ def test_list_overflow_recovers_from_a_checkpoint():
     assert np.array_equal(o1, o2)
     for kk, e in errs.items():
         assert e <= TOL_STEP, (kk, e)
+
+@pytest.mark.parametrize("n,walls,kernel,n_cells", [
+    ((8, 9, 10), -1, 4, 1),      # the first tile holds nodes on both sides of a seam
+    ((9, 10, 17), -1, 2, 1),
+    ((5, 24, 7), -1, 4, 1),      # axes of a single tile
+    ((10, 19, 9), 1, 4, 1),
+    ((11, 25, 8), 2, 4, 1),
+    ((24, 24, 24), -1, 4, 6),    # tiles of more than 512 entries
+])
+def test_lattice_pass_small_axes_and_chunks(n, walls, kernel, n_cells):
+    """One step where the in-tile runs of the stencils wrap, end at a wall or
+    come in several chunks, against the FP64 oracle."""
+    w = tiny_periodic(seed=91, n=n, n_cells=n_cells, walls=walls, ibm_kernel=kernel)
+    rng = np.random.default_rng(92)
+    cells = jitter_cells(rng, w.cells, 0.05)
+    if n_cells > 1:   # all about one point
+        cells.origin[:] = cells.origin[0] + rng.integers(-1, 2, cells.origin.shape)
+    g0 = random_shifted_populations(rng, w.lattice, 1e-3)
+    sim = make_sim(w, cells)
+    sim.write_populations(g0)
+    sim.step(1)
+    sim.sync()
+    f1, X1, info = step.step(oracle_model(w, cells), *oracle_state(g0, cells))
+    errs = {"g": relerr(sim.read_populations(), lattice.shifted(f1)),
+            "F": relerr(sim.read_force_field(), info["F"]),
+            "U": relerr(sim.read_vertex_velocity(), info["U"])}
+    print(n, walls, kernel, n_cells, errs, flush=True)
+    for k, e in errs.items():
+        assert e <= TOL_STEP, (k, e)
