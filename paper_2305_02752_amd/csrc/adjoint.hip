@@ -216,7 +216,7 @@ __global__ __launch_bounds__(256) void k_adj_collide(const float* __restrict__ l
 
 // Batched form: box blockIdx.y (the grid's x extent is every box's own).
 __global__ __launch_bounds__(256) void k_adj_collide_multi(const AdjCollideArgs* __restrict__ many) {
-  const AdjCollideArgs& a = many[blockIdx.y];
+  const AdjCollideArgs& a = launch_record(many, blockIdx.y);
   adj_collide_body<const Lattice&>(a.lam1, a.lam0, a.h0, a.F, a.lamu, a.lamF, a.domega_part, a.mask,
                                    a.domega_in_part, a.L);
 }
@@ -297,7 +297,7 @@ __global__ __launch_bounds__(256) void k_adj_vertex(Cells C, Mesh M, Lattice L,
 }
 
 __global__ __launch_bounds__(256) void k_adj_vertex_multi(const AdjVertexArgs* __restrict__ many) {
-  const AdjVertexArgs& a = many[blockIdx.y];
+  const AdjVertexArgs& a = launch_record(many, blockIdx.y);
   adj_vertex_body(a.C, a.M, a.L, a.lamX1, a.macro, a.lamF, a.lamFv, a.lamX0);
 }
 
@@ -455,7 +455,7 @@ __global__ __launch_bounds__(kAdjThreads) void k_adj_membrane(Cells C, Mesh M,
 
 template <int kAdjThreads>
 __global__ __launch_bounds__(kAdjThreads) void k_adj_membrane_multi(const AdjMembraneArgs* __restrict__ many) {
-  const AdjMembraneArgs& a = many[blockIdx.y];
+  const AdjMembraneArgs& a = launch_record(many, blockIdx.y);
   adj_membrane_body<kAdjThreads>(a.C, a.M, a.lamFv, a.lamX, a.dk);
 }
 

@@ -34,7 +34,7 @@ __global__ __launch_bounds__(kThreads) void k_bin_vertices(Cells C, Mesh M, Latt
 // Batched form: box blockIdx.y.
 template <int kThreads>
 __global__ __launch_bounds__(kThreads) void k_bin_vertices_multi(const BinArgs* __restrict__ many) {
-  const BinArgs& a = many[blockIdx.y];
+  const BinArgs& a = launch_record(many, blockIdx.y);
   bin_vertices_body<false>(a.C, a.M, a.L, a.B);
 }
 

@@ -139,7 +139,7 @@ __global__ __launch_bounds__(kCellThreads) void k_cell_step(Cells C, Mesh M, Lat
 // Batched form: box blockIdx.y.
 template <int K, int kCellThreads>
 __global__ __launch_bounds__(kCellThreads) void k_cell_step_multi(const CellStepArgs* __restrict__ many) {
-  const CellStepArgs& a = many[blockIdx.y];
+  const CellStepArgs& a = launch_record(many, blockIdx.y);
   cell_step_body<K, kCellThreads, false>(a.C, a.M, a.L, a.B, a.partial, a.flags, a.advect, a.src, a.refresh,
                                          a.ab2, a.recentre, 0);
 }

@@ -46,6 +46,16 @@ __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// Record i of a device array that no kernel of the launch writes.  Read
+// through the constant address space, its fields come by scalar loads into
+// scalar registers; through a plain pointer the kernel's own stores might
+// change them, and every lane loads and keeps its own copy.
+template <class T>
+__device__ __forceinline__ const T& launch_record(const T* many, unsigned i) {
+  typedef const __attribute__((address_space(4))) T* constant_ptr;
+  return *(const T*)(constant_ptr)(unsigned long long)(many + i);
+}
+
 [[maybe_unused]] static __device__ __noinline__ void fix_add3_wide(long long* a0, long long* a1,
                                                                    long long* a2, float x, float y,
                                                                    float z) {

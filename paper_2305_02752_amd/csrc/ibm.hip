@@ -294,7 +294,7 @@ __global__ __launch_bounds__(256) void k_spread(Cells C, Mesh M, Lattice L, Bins
 
 template <int K>
 __global__ __launch_bounds__(256) void k_spread_multi(const SpreadArgs* __restrict__ many) {
-  const SpreadArgs& a = many[blockIdx.y];
+  const SpreadArgs& a = launch_record(many, blockIdx.y);
   spread_body<K>(a.C, a.M, a.L, a.B, a.vec, a.body, a.F);
 }
 
@@ -774,8 +774,11 @@ __device__ __forceinline__ void interp(int m, const Lattice& L, const Smem<LE>& 
 
 }  // namespace srt
 
+constexpr int kNoWall = -1, kAnyWall = 3;
+
 // The fused lattice pass, one work-group per tile, with the sorted-entry IBM
-// phases (W: with walls; LE: with sheared images and two or more tiles along
+// phases (WA: the wall axis, kNoWall, or kAnyWall when boxes of one launch may
+// differ in it; LE: with sheared images and two or more tiles along
 // z, which leave an entry's nodes in one image):
 //  1. stage the tile's entries (records ordered by in-tile box shape) and
 //     spread their forces into LDS (int32 fixed point at the tile's scale);
@@ -796,10 +799,14 @@ __device__ __forceinline__ void interp(int m, const Lattice& L, const Smem<LE>& 
 // (the scale then comes from a first pass over all their forces, and the
 // interpolation stages again every chunk but the last).
 // The struct arguments come by value from the single-box kernel (its own
-// parameters) and by reference to global memory from the batched one: a
-// reference to a kernel's by-value parameter, or a by-value copy of a record
-// in global memory, would put the lattice record in scratch.
-template <int K, bool W, bool LE, class CT, class MT, class LT, class BT>
+// parameters) and by reference to constant memory from the batched one
+// (launch_record: 60 vector registers, 106 through a plain reference; with
+// six waves per SIMD then 238 us for 255 on 64 boxes of 48^3): a reference to
+// a kernel's by-value parameter, or a by-value copy of a record in global
+// memory, would put the lattice record in scratch.  The wall axis is a
+// compile-time choice of the single-box kernel: 52.5 us for 54.5 on a walled
+// 128 x 64 x 64, 19.6 for 21.4 on 32^3.
+template <int K, int WA, bool LE, class CT, class MT, class LT, class BT>
 __device__ __forceinline__ void tile_step_sorted_body(CT C, MT M, LT L, BT B,
                                                       const float* __restrict__ gin,
                                                       float* __restrict__ gout, float* __restrict__ F,
@@ -807,6 +814,8 @@ __device__ __forceinline__ void tile_step_sorted_body(CT C, MT M, LT L, BT B,
                                                       float4* __restrict__ partial, int fields,
                                                       unsigned char* __restrict__ mask) {
   __shared__ srt::Smem<LE> S;
+  constexpr bool W = WA != kNoWall;
+  const int wa = WA == kAnyWall ? L.wall_axis : WA;
   const int t = tile_of_block(L, blockIdx.x);
   if (t < 0) return;
   int x0, y0, z0;
@@ -869,8 +878,8 @@ __device__ __forceinline__ void tile_step_sorted_body(CT C, MT M, LT L, BT B,
     // wall layers: a source past the wall is the opposite population at the node itself
     bool lo = false, hi = false;
     if (W) {
-      const int c = L.wall_axis == 0 ? x : (L.wall_axis == 1 ? y : z);
-      const int n = L.wall_axis == 0 ? L.nx : (L.wall_axis == 1 ? L.ny : L.nz);
+      const int c = wa == 0 ? x : (wa == 1 ? y : z);
+      const int n = wa == 0 ? L.nx : (wa == 1 ? L.ny : L.nz);
       lo = c == 0;
       hi = c == n - 1;
     }
@@ -879,7 +888,7 @@ __device__ __forceinline__ void tile_step_sorted_body(CT C, MT M, LT L, BT B,
     for (int q = 0; q < kQ; ++q) {
       const unsigned src = SX[lbm::cx[q] + 1] + SY[lbm::cy[q] + 1] + SZ[lbm::cz[q] + 1];
       if (W) {
-        const int ew = L.wall_axis == 0 ? lbm::cx[q] : (L.wall_axis == 1 ? lbm::cy[q] : lbm::cz[q]);
+        const int ew = wa == 0 ? lbm::cx[q] : (wa == 1 ? lbm::cy[q] : lbm::cz[q]);
         const bool past = (ew == 1 && lo) || (ew == -1 && hi);
         g[q] = past ? gin[(int64_t)lbm::opp[q] * NP + hl] : gin[(int64_t)q * NP + src];
       } else if (LE && !L.le_raw && ((lbm::cz[q] > 0 && z == 0) || (lbm::cz[q] < 0 && z == L.nz - 1))) {
@@ -915,7 +924,7 @@ __device__ __forceinline__ void tile_step_sorted_body(CT C, MT M, LT L, BT B,
     for (int q = 0; q < kQ; ++q) {
       float v = g[q];
       if (W) {   // the value heading into a moving wall carries Ladd's term
-        const int ew = L.wall_axis == 0 ? lbm::cx[q] : (L.wall_axis == 1 ? lbm::cy[q] : lbm::cz[q]);
+        const int ew = wa == 0 ? lbm::cx[q] : (wa == 1 ? lbm::cy[q] : lbm::cz[q]);
         if (ew == -1 && lo) v += L.wc_lo[q] * rho;
         if (ew == 1 && hi) v += L.wc_hi[q] * rho;
       }
@@ -945,7 +954,7 @@ __device__ __forceinline__ void tile_step_sorted_body(CT C, MT M, LT L, BT B,
   }
 }
 
-template <int K, bool W>
+template <int K, int WA>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void k_tile_step_sorted(
     Cells C, Mesh M, Lattice L, Bins B,
                                                           const float* __restrict__ gin,
@@ -954,7 +963,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void k
                                                           float4* __restrict__ macro,
                                                           float4* __restrict__ partial, int fields,
                                                           unsigned char* __restrict__ mask) {
-  tile_step_sorted_body<K, W, false, Cells, Mesh, Lattice, Bins>(C, M, L, B, gin, gout, F, macro, partial, fields,
+  tile_step_sorted_body<K, WA, false, Cells, Mesh, Lattice, Bins>(C, M, L, B, gin, gout, F, macro, partial, fields,
                                                                  mask);
 }
 
@@ -968,15 +977,15 @@ __global__ __launch_bounds__(256) void k_tile_step_sorted_le(Cells C, Mesh M, La
                                                              float4* __restrict__ macro,
                                                              float4* __restrict__ partial, int fields,
                                                              unsigned char* __restrict__ mask) {
-  tile_step_sorted_body<K, false, true, Cells, Mesh, Lattice, Bins>(C, M, L, B, gin, gout, F, macro, partial, fields,
+  tile_step_sorted_body<K, kNoWall, true, Cells, Mesh, Lattice, Bins>(C, M, L, B, gin, gout, F, macro, partial, fields,
                                                                     mask);
 }
 
 // Batched form: box blockIdx.y.
-template <int K, bool W>
-__global__ __launch_bounds__(256) void k_tile_step_sorted_multi(const TileStepArgs* __restrict__ many) {
-  const TileStepArgs& a = many[blockIdx.y];
-  tile_step_sorted_body<K, W, false, const Cells&, const Mesh&, const Lattice&, const Bins&>(
+template <int K, int WA>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void k_tile_step_sorted_multi(const TileStepArgs* __restrict__ many) {
+  const TileStepArgs& a = launch_record(many, blockIdx.y);
+  tile_step_sorted_body<K, WA, false, const Cells&, const Mesh&, const Lattice&, const Bins&>(
       a.C, a.M, a.L, a.B, a.gin, a.gout, a.F, a.macro, a.partial, a.fields, a.mask);
 }
 
@@ -1095,11 +1104,11 @@ hipError_t launch_tile_step_multi(const TileStepArgs& a0, const TileStepArgs* de
   const dim3 grid((unsigned)tile_grid(a0.L), (unsigned)n);
   const bool w = a0.L.wall_axis >= 0;
   if (a0.L.kernel == 4) {
-    if (w) hipLaunchKernelGGL((k_tile_step_sorted_multi<4, true>), grid, dim3(256), 0, s, dev);
-    else hipLaunchKernelGGL((k_tile_step_sorted_multi<4, false>), grid, dim3(256), 0, s, dev);
+    if (w) hipLaunchKernelGGL((k_tile_step_sorted_multi<4, kAnyWall>), grid, dim3(256), 0, s, dev);
+    else hipLaunchKernelGGL((k_tile_step_sorted_multi<4, kNoWall>), grid, dim3(256), 0, s, dev);
   } else {
-    if (w) hipLaunchKernelGGL((k_tile_step_sorted_multi<2, true>), grid, dim3(256), 0, s, dev);
-    else hipLaunchKernelGGL((k_tile_step_sorted_multi<2, false>), grid, dim3(256), 0, s, dev);
+    if (w) hipLaunchKernelGGL((k_tile_step_sorted_multi<2, kAnyWall>), grid, dim3(256), 0, s, dev);
+    else hipLaunchKernelGGL((k_tile_step_sorted_multi<2, kNoWall>), grid, dim3(256), 0, s, dev);
   }
   return hipGetLastError();
 }
@@ -1107,33 +1116,21 @@ hipError_t launch_tile_step_multi(const TileStepArgs& a0, const TileStepArgs* de
 hipError_t launch_tile_step(const Cells& c, const Mesh& m, const Lattice& L, const Bins& b,
                             const float* gin, float* gout, float* F, float4* macro, float4* partial,
                             bool fields, unsigned char* mask, hipStream_t s) {
-  const dim3 grid((unsigned)tile_grid(L));
-  const int fl = fields ? 1 : 0;
-  if (L.le && L.tz == 1) {   // an entry's nodes may lie in two images
-    if (L.kernel == 4)
-      hipLaunchKernelGGL(k_tile_step_le_thin<4>, grid, dim3(256), 0, s, c, m, L, b, gin, gout, F, macro, partial,
-                         fl, mask);
-    else
-      hipLaunchKernelGGL(k_tile_step_le_thin<2>, grid, dim3(256), 0, s, c, m, L, b, gin, gout, F, macro, partial,
-                         fl, mask);
-  } else if (L.kernel == 4 && L.le)
-    hipLaunchKernelGGL(k_tile_step_sorted_le<4>, grid, dim3(256), 0, s, c, m, L, b, gin, gout, F,
-                       macro, partial, fl, mask);
-  else if (L.kernel == 4 && L.wall_axis >= 0)
-    hipLaunchKernelGGL((k_tile_step_sorted<4, true>), grid, dim3(256), 0, s, c, m, L, b, gin, gout, F,
-                       macro, partial, fl, mask);
-  else if (L.kernel == 4)
-    hipLaunchKernelGGL((k_tile_step_sorted<4, false>), grid, dim3(256), 0, s, c, m, L, b, gin, gout, F,
-                       macro, partial, fl, mask);
-  else if (L.le)
-    hipLaunchKernelGGL(k_tile_step_sorted_le<2>, grid, dim3(256), 0, s, c, m, L, b, gin, gout, F,
-                       macro, partial, fl, mask);
-  else if (L.wall_axis >= 0)
-    hipLaunchKernelGGL((k_tile_step_sorted<2, true>), grid, dim3(256), 0, s, c, m, L, b, gin, gout, F,
-                       macro, partial, fl, mask);
-  else
-    hipLaunchKernelGGL((k_tile_step_sorted<2, false>), grid, dim3(256), 0, s, c, m, L, b, gin, gout, F,
-                       macro, partial, fl, mask);
+  auto go = [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3((unsigned)tile_grid(L)), dim3(256), 0, s, c, m, L, b, gin, gout, F, macro, partial,
+                       fields ? 1 : 0, mask);
+  };
+  auto form = [&](auto k) {
+    constexpr int K = decltype(k)::value;
+    if (L.le && L.tz == 1) go(k_tile_step_le_thin<K>);   // an entry's nodes may lie in two images
+    else if (L.le) go(k_tile_step_sorted_le<K>);
+    else if (L.wall_axis == 0) go(k_tile_step_sorted<K, 0>);
+    else if (L.wall_axis == 1) go(k_tile_step_sorted<K, 1>);
+    else if (L.wall_axis == 2) go(k_tile_step_sorted<K, 2>);
+    else go(k_tile_step_sorted<K, kNoWall>);
+  };
+  if (L.kernel == 4) form(std::integral_constant<int, 4>());
+  else form(std::integral_constant<int, 2>());
   return hipGetLastError();
 }
 
