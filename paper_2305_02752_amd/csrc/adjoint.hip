@@ -26,6 +26,7 @@
 // The IBM kernel must be the 4-point phi4 (C^1); the linear hat has no
 // derivative at the nodes.
 #include <algorithm>
+#include <type_traits>
 
 #include "common.h"
 #include "lbm_dev.h"
@@ -52,9 +53,18 @@ __device__ __forceinline__ double wq64(int j) { return j == 0 ? 1.0 / 3 : (j < 7
 // full-size gradient by about 1% of its difference from the oracle's and
 // takes the kernel from 416 to 264 bytes per site.
 // LT: the lattice record by value (single-box kernel) or by reference to
-// global memory (batched kernel), so that neither puts it in scratch.
-template <class LT>
-__device__ __forceinline__ void adj_collide_body(const float* __restrict__ lam1, float* __restrict__ lam0,
+// constant memory (batched kernel), so that neither puts it in scratch.
+// WA: the wall axis, -1 without one.
+// Bound by the populations' traffic (264 bytes per site); the stores of
+// lam_f scatter to the neighbouring sites, so neighbouring blocks have to sit
+// on one XCD (block_of): rows shared by two tiles written from two XCDs
+// reach memory as partial lines twice.  With that, a compile-time wall axis and
+// the sources formed again instead of kept (206 vector registers, 2 waves per
+// SIMD; now 120, 4) 64 boxes of 48^3 take 415 us for 574 (4.5 TB/s), one
+// of 32^3 6.3 for 11.
+template <int WA, class LT>
+__device__ __forceinline__ void adj_collide_body(int blk, int nblk,
+                                                 const float* __restrict__ lam1, float* __restrict__ lam0,
                                                  const float* __restrict__ h0, const float* __restrict__ F,
                                                  const float* __restrict__ lamu, float* __restrict__ lamF,
                                                  double* __restrict__ domega_part,
@@ -62,7 +72,7 @@ __device__ __forceinline__ void adj_collide_body(const float* __restrict__ lam1,
                                                  double* __restrict__ domega_in_part, LT L) {
   __shared__ double red[1 + kVisClasses][4];
   const int64_t N = L.np;   // slots of every (tile-major) lattice field
-  const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t s = (int64_t)blk * blockDim.x + threadIdx.x;
   double dom = 0.0, dom_in = 0.0;
   int cls = -1;   // viscosity class of an interior site
   int x, y, z;
@@ -88,23 +98,24 @@ __device__ __forceinline__ void adj_collide_body(const float* __restrict__ lam1,
     const int ym = y == 0 ? L.ny - 1 : y - 1, yp = y == L.ny - 1 ? 0 : y + 1;
     const int zm = z == 0 ? L.nz - 1 : z - 1, zp = z == L.nz - 1 ? 0 : z + 1;
     const unsigned py = (unsigned)L.tx << 9, pz = py * (unsigned)L.ty;
-    const unsigned SX[3] = {(unsigned)(((xp >> 3) << 9) | (xp & 7)), (unsigned)(((x >> 3) << 9) | (x & 7)),
+    unsigned SX[3] = {(unsigned)(((xp >> 3) << 9) | (xp & 7)), (unsigned)(((x >> 3) << 9) | (x & 7)),
                             (unsigned)(((xm >> 3) << 9) | (xm & 7))};
-    const unsigned SY[3] = {(unsigned)(yp >> 3) * py + (unsigned)((yp & 7) << 3),
+    unsigned SY[3] = {(unsigned)(yp >> 3) * py + (unsigned)((yp & 7) << 3),
                             (unsigned)(y >> 3) * py + (unsigned)((y & 7) << 3),
                             (unsigned)(ym >> 3) * py + (unsigned)((ym & 7) << 3)};
-    const unsigned SZ[3] = {(unsigned)(zp >> 3) * pz + (unsigned)((zp & 7) << 6),
+    unsigned SZ[3] = {(unsigned)(zp >> 3) * pz + (unsigned)((zp & 7) << 6),
                             (unsigned)(z >> 3) * pz + (unsigned)((z & 7) << 6),
                             (unsigned)(zm >> 3) * pz + (unsigned)((zm & 7) << 6)};
-    const unsigned hl = SX[1] + SY[1] + SZ[1];   // this node (== s)
-    const int wa = L.wall_axis;
+    unsigned hl = SX[1] + SY[1] + SZ[1];   // this node (== s)
+    constexpr int wa = WA;
+    constexpr bool W = WA >= 0;
     const int wc = wa == 0 ? x : (wa == 1 ? y : z), wn = wa == 0 ? L.nx : (wa == 1 ? L.ny : L.nz);
-    const bool wlo = wa >= 0 && wc == 0, whi = wa >= 0 && wc == wn - 1;
+    const bool wlo = W && wc == 0, whi = W && wc == wn - 1;
     // element offset of the value pulled into direction q
     auto source = [&](int q) -> int64_t {
       const int ex = cx[q], ey = cy[q], ez = cz[q];
       const int ew = wa == 0 ? ex : (wa == 1 ? ey : ez);
-      if ((ew == 1 && wlo) || (ew == -1 && whi)) return (int64_t)opp[q] * N + hl;
+      if (W && ((ew == 1 && wlo) || (ew == -1 && whi))) return (int64_t)opp[q] * N + hl;
       const unsigned sx = ex > 0 ? SX[2] : (ex < 0 ? SX[0] : SX[1]);
       const unsigned sy = ey > 0 ? SY[2] : (ey < 0 ? SY[0] : SY[1]);
       const unsigned sz = ez > 0 ? SZ[2] : (ez < 0 ? SZ[0] : SZ[1]);
@@ -123,13 +134,17 @@ __device__ __forceinline__ void adj_collide_body(const float* __restrict__ lam1,
 #pragma unroll
     for (int j = 0; j < kQ; ++j) {
       const double gj = h0[source(j)];
-      const double l = lam1[j * N + s];
+      const double l = lam1[j * N + hl];
       // (terms of zero directions are left out, not added as zeros)
       drho += gj;
       if (cx[j] != 0) jx += cx[j] * gj;
       if (cy[j] != 0) jy += cy[j] * gj;
       if (cz[j] != 0) jz += cz[j] * gj;
-      lrho += (double)lbm::wall_coeff(L, j, x, y, z) * l;
+      if (W) {   // Ladd's coefficient of a population leaving through a wall
+        const int ew = wa == 0 ? cx[j] : (wa == 1 ? cy[j] : cz[j]);
+        if (ew == -1 && wlo) lrho += (double)L.wc_lo[j] * l;
+        if (ew == 1 && whi) lrho += (double)L.wc_hi[j] * l;
+      }
       Pg += l * gj;
       const double wl = wq64(j) * l;
       M0 += wl;
@@ -176,32 +191,45 @@ __device__ __forceinline__ void adj_collide_body(const float* __restrict__ lam1,
     Bx += lamu[s];
     By += lamu[N + s];
     Bz += lamu[2 * N + s];
+    // the sources are formed again rather than kept through the contraction
+    asm volatile("" : "+v"(SX[0]), "+v"(SX[1]), "+v"(SX[2]), "+v"(SY[0]), "+v"(SY[1]), "+v"(SY[2]), "+v"(SZ[0]),
+                 "+v"(SZ[1]), "+v"(SZ[2]), "+v"(hl));
 #pragma unroll
     for (int i = 0; i < kQ; ++i)
-      lam0[source(i)] = (float)((1.0 - om) * (double)lam1[i * N + s] + A +
+      lam0[source(i)] = (float)((1.0 - om) * (double)lam1[i * N + hl] + A +
                                 (Bx * (cx[i] - ux) + By * (cy[i] - uy) + Bz * (cz[i] - uz)) * inv);
     lamF[s] = (float)(Gx + 0.5 * Bx * inv);
     lamF[N + s] = (float)(Gy + 0.5 * By * inv);
     lamF[2 * N + s] = (float)(Gz + 0.5 * Bz * inv);
   }
   // per-block sums for the plasma sites and for each viscosity class, in a
-  // fixed order (each block owns its slots across steps)
-  for (int k = -1; k < kVisClasses; ++k) {
+  // fixed order (each block owns its slots across steps); without marks no
+  // site has a class
+  const int nk = mask ? kVisClasses : 0;
+  for (int k = -1; k < nk; ++k) {
     double v = k < 0 ? dom : (cls == k ? dom_in : 0.0);
     for (int m = kWave / 2; m > 0; m >>= 1) v += __shfl_xor(v, m);
     if ((threadIdx.x & (kWave - 1)) == 0) red[k + 1][threadIdx.x / kWave] = v;
   }
   __syncthreads();
-  if (threadIdx.x < 1 + kVisClasses) {
+  if ((int)threadIdx.x < 1 + nk) {
     double t = 0.0;
     for (int w = 0; w < (int)(blockDim.x / kWave); ++w) t += red[threadIdx.x][w];
     if (threadIdx.x == 0)
-      domega_part[blockIdx.x] += t;
+      domega_part[blk] += t;
     else
-      domega_in_part[(int64_t)(threadIdx.x - 1) * gridDim.x + blockIdx.x] += t;
+      domega_in_part[(int64_t)(threadIdx.x - 1) * nblk + blk] += t;
   }
 }
 
+// Block b of `total` in the order that gives each XCD (work-groups go to
+// them round-robin) one contiguous range; `total` or more for padding.
+__device__ __forceinline__ unsigned block_of(unsigned b, unsigned total) {
+  return (b & 7) * ((total + 7) >> 3) + (b >> 3);
+}
+inline unsigned padded_blocks(unsigned total) { return ((total + 7) >> 3) * 8; }
+
+template <int WA>
 __global__ __launch_bounds__(256) void k_adj_collide(const float* __restrict__ lam1,
                                                      float* __restrict__ lam0,
                                                      const float* __restrict__ h0,
@@ -210,81 +238,109 @@ __global__ __launch_bounds__(256) void k_adj_collide(const float* __restrict__ l
                                                      float* __restrict__ lamF,
                                                      double* __restrict__ domega_part,
                                                      unsigned char* __restrict__ mask,
-                                                     double* __restrict__ domega_in_part, Lattice L) {
-  adj_collide_body<Lattice>(lam1, lam0, h0, F, lamu, lamF, domega_part, mask, domega_in_part, L);
+                                                     double* __restrict__ domega_in_part, Lattice L, int nblk) {
+  const unsigned blk = block_of(blockIdx.x, nblk);
+  if (blk >= (unsigned)nblk) return;
+  adj_collide_body<WA, Lattice>(blk, nblk, lam1, lam0, h0, F, lamu, lamF, domega_part, mask, domega_in_part, L);
 }
 
-// Batched form: box blockIdx.y (the grid's x extent is every box's own).
-__global__ __launch_bounds__(256) void k_adj_collide_multi(const AdjCollideArgs* __restrict__ many) {
-  const AdjCollideArgs& a = launch_record(many, blockIdx.y);
-  adj_collide_body<const Lattice&>(a.lam1, a.lam0, a.h0, a.F, a.lamu, a.lamF, a.domega_part, a.mask,
-                                   a.domega_in_part, a.L);
+// Batched form: n boxes of nblk blocks each, box after box, so that a box (or
+// a run of its tiles, when the boxes are few) stays on one XCD.
+template <int WA>
+__global__ __launch_bounds__(256) void k_adj_collide_multi(const AdjCollideArgs* __restrict__ many, int nblk, int n) {
+  const unsigned all = block_of(blockIdx.x, (unsigned)nblk * n);
+  if (all >= (unsigned)nblk * n) return;
+  const unsigned box = all / (unsigned)nblk;
+  const AdjCollideArgs& a = launch_record(many, box);
+  adj_collide_body<WA, const Lattice&>(all - box * nblk, nblk, a.lam1, a.lam0, a.h0, a.F, a.lamu, a.lamF,
+                                           a.domega_part, a.mask, a.domega_in_part, a.L);
 }
 
-__device__ __forceinline__ void adj_vertex_body(Cells C, Mesh M, Lattice L,
-                                                const float* __restrict__ lamX1,
+// Sum over a row of 16 lanes (all active), the same in each of them: lane
+// swaps xor 1, xor 2, then the mirrored half-row and row.
+template <int CTRL>
+__device__ __forceinline__ double swap_add(double v) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xF, 0xF, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xF, 0xF, false);
+  return v + __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+__device__ __forceinline__ float row16_sum(double v) {
+  return (float)swap_add<0x140>(swap_add<0x141>(swap_add<0x4E>(swap_add<0xB1>(v))));
+}
+
+// Sixteen lanes per vertex, one row of four x nodes each: a thread that
+// walked all 64 nodes waited for its gathers one row after another, and a
+// box's 642 vertices filled three work-groups (one box of 32^3: 31 us, now 7;
+// 64 of 48^3: 42, now 36).  Summed in FP64, which costs nothing beside the
+// gathers.
+constexpr int kVertexLanes = 16;
+template <class CT, class MT, class LT>
+__device__ __forceinline__ void adj_vertex_body(CT C, MT M, LT L, const float* __restrict__ lamX1,
                                                 const float4* __restrict__ macro,
                                                 const float* __restrict__ lamF, float* __restrict__ lamFv,
                                                 float* __restrict__ lamX0) {
-  const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (v >= (int64_t)C.n * M.nv) return;
+  const int64_t nv = (int64_t)C.n * M.nv;
+  const int64_t id = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kVertexLanes;
+  const int64_t v = id < nv ? id : nv - 1;   // whole rows stay active for the sums
+  const int lane = threadIdx.x & (kVertexLanes - 1), ky = lane & 3, kz = lane >> 2;
   const int c = (int)(v / M.nv);
   const int64_t N = L.np;
-  const int n3[3] = {L.nx, L.ny, L.nz};
-  int base[3];
-  float w[3][4], dw[3][4];
-#pragma unroll
-  for (int d = 0; d < 3; ++d) {
-    const float x = C.off[v * 3 + d];
+  // node, side past a wall, weight and its derivative of stencil position k
+  auto axis = [&](int o, float x, int n, int wall, int k, int& p, int& side, float& w, float& dw) {
     const float fl = floorf(x);
-    base[d] = C.origin[3 * c + d] + (int)fl - 1;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      w[d][k] = phi4(x - fl + 1.f - (float)k);
-      dw[d][k] = dphi4(x - fl + 1.f - (float)k);
-    }
-  }
+    p = o + (int)fl - 1 + k;
+    side = wall ? (p < 0 ? 1 : (p >= n ? 2 : 0)) : 0;
+    if (!wall) p = wrap(p, n);
+    w = phi4(x - fl + 1.f - (float)k);
+    dw = dphi4(x - fl + 1.f - (float)k);
+  };
+  int py, pz, sy, sz;
+  float wy, wz, dwy, dwz;
+  axis(C.origin[3 * c + 1], C.off[v * 3 + 1], L.ny, L.bc[1] == 1, ky, py, sy, wy, dwy);
+  axis(C.origin[3 * c + 2], C.off[v * 3 + 2], L.nz, L.bc[2] == 1, kz, pz, sz, wz, dwz);
+  const int ox = C.origin[3 * c];
+  const float x = C.off[v * 3];
   const float lux = lamX1[3 * v], luy = lamX1[3 * v + 1], luz = lamX1[3 * v + 2];
   const float Fx = C.force[3 * v], Fy = C.force[3 * v + 1], Fz = C.force[3 * v + 2];
-  float sFx = 0.f, sFy = 0.f, sFz = 0.f, gx = 0.f, gy = 0.f, gz = 0.f;
-  for (int kz = 0; kz < 4; ++kz) {
-    int pz = base[2] + kz, side = 0;
-    if (L.bc[2] == 1) side |= pz < 0 ? 1 : (pz >= n3[2] ? 2 : 0); else pz = wrap(pz, n3[2]);
-    for (int ky = 0; ky < 4; ++ky) {
-      int py = base[1] + ky, sy = 0;
-      if (L.bc[1] == 1) sy = py < 0 ? 1 : (py >= n3[1] ? 2 : 0); else py = wrap(py, n3[1]);
-      for (int kx = 0; kx < 4; ++kx) {
-        int px = base[0] + kx, sx = 0;
-        if (L.bc[0] == 1) sx = px < 0 ? 1 : (px >= n3[0] ? 2 : 0); else px = wrap(px, n3[0]);
-        const int sd = side | sy | sx;
-        float ux, uy, uz, lFx = 0.f, lFy = 0.f, lFz = 0.f;
-        if (sd == 1) {
-          ux = L.ulo[0]; uy = L.ulo[1]; uz = L.ulo[2];
-        } else if (sd == 2) {
-          ux = L.uhi[0]; uy = L.uhi[1]; uz = L.uhi[2];
-        } else {
-          const int64_t s = site_of(L, px, py, pz);
-          const float4 q = macro[s];
-          ux = q.x; uy = q.y; uz = q.z;
-          lFx = lamF[s]; lFy = lamF[N + s]; lFz = lamF[2 * N + s];
-        }
-        const float W = w[0][kx] * w[1][ky] * w[2][kz];
-        sFx += W * lFx;
-        sFy += W * lFy;
-        sFz += W * lFz;
-        const float a = lux * ux + luy * uy + luz * uz + Fx * lFx + Fy * lFy + Fz * lFz;
-        gx += a * dw[0][kx] * w[1][ky] * w[2][kz];
-        gy += a * w[0][kx] * dw[1][ky] * w[2][kz];
-        gz += a * w[0][kx] * w[1][ky] * dw[2][kz];
-      }
+  double sFx = 0., sFy = 0., sFz = 0., gx = 0., gy = 0., gz = 0.;
+#pragma unroll
+  for (int kx = 0; kx < 4; ++kx) {
+    int px, sx;
+    float wx, dwx;
+    axis(ox, x, L.nx, L.bc[0] == 1, kx, px, sx, wx, dwx);
+    const int sd = sz | sy | sx;
+    float ux, uy, uz, lFx = 0.f, lFy = 0.f, lFz = 0.f;
+    if (sd == 1) {
+      ux = L.ulo[0]; uy = L.ulo[1]; uz = L.ulo[2];
+    } else if (sd == 2) {
+      ux = L.uhi[0]; uy = L.uhi[1]; uz = L.uhi[2];
+    } else {
+      const int64_t s = site_of(L, px, py, pz);
+      const float4 q = macro[s];
+      ux = q.x; uy = q.y; uz = q.z;
+      lFx = lamF[s]; lFy = lamF[N + s]; lFz = lamF[2 * N + s];
     }
+    const double W = (double)wx * wy * wz;
+    sFx += W * lFx;
+    sFy += W * lFy;
+    sFz += W * lFz;
+    const double a = (double)lux * ux + (double)luy * uy + (double)luz * uz + (double)Fx * lFx + (double)Fy * lFy +
+                     (double)Fz * lFz;
+    gx += a * dwx * wy * wz;
+    gy += a * wx * dwy * wz;
+    gz += a * wx * wy * dwz;
   }
-  lamFv[3 * v] = sFx;
-  lamFv[3 * v + 1] = sFy;
-  lamFv[3 * v + 2] = sFz;
-  lamX0[3 * v] = lux + gx;
-  lamX0[3 * v + 1] = luy + gy;
-  lamX0[3 * v + 2] = luz + gz;
+  const float3 f = make_float3(row16_sum(sFx), row16_sum(sFy), row16_sum(sFz));
+  const float3 g = make_float3(row16_sum(gx), row16_sum(gy), row16_sum(gz));
+  if (lane == 0 && id < nv) {
+    lamFv[3 * v] = f.x;
+    lamFv[3 * v + 1] = f.y;
+    lamFv[3 * v + 2] = f.z;
+    lamX0[3 * v] = lux + g.x;
+    lamX0[3 * v + 1] = luy + g.y;
+    lamX0[3 * v + 2] = luz + g.z;
+  }
 }
 
 __global__ __launch_bounds__(256) void k_adj_vertex(Cells C, Mesh M, Lattice L,
@@ -293,12 +349,12 @@ __global__ __launch_bounds__(256) void k_adj_vertex(Cells C, Mesh M, Lattice L,
                                                     const float* __restrict__ lamF,
                                                     float* __restrict__ lamFv,
                                                     float* __restrict__ lamX0) {
-  adj_vertex_body(C, M, L, lamX1, macro, lamF, lamFv, lamX0);
+  adj_vertex_body<Cells, Mesh, Lattice>(C, M, L, lamX1, macro, lamF, lamFv, lamX0);
 }
 
 __global__ __launch_bounds__(256) void k_adj_vertex_multi(const AdjVertexArgs* __restrict__ many) {
   const AdjVertexArgs& a = launch_record(many, blockIdx.y);
-  adj_vertex_body(a.C, a.M, a.L, a.lamX1, a.macro, a.lamF, a.lamFv, a.lamX0);
+  adj_vertex_body<const Cells&, const Mesh&, const Lattice&>(a.C, a.M, a.L, a.lamX1, a.macro, a.lamF, a.lamFv, a.lamX0);
 }
 
 __device__ inline V3<Dual> ldd(const float* p, const float* t, int i) {
@@ -495,12 +551,19 @@ __global__ __launch_bounds__(64) void k_loss_seed(Cells C, Mesh M, const double*
   }
 }
 
-__global__ void k_sum_parts(const double* __restrict__ parts, int n, double* __restrict__ out) {
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    double t = 0.0;
-    for (int i = 0; i < n; ++i) t += parts[i];   // fixed order
-    *out = t;
+// One work-group of 256, in a fixed order: strided sums, then a tree.  (One
+// thread adding 432 parts took 34 us, once per box; 3 us.)
+__global__ __launch_bounds__(256) void k_sum_parts(const double* __restrict__ parts, int n,
+                                                   double* __restrict__ out) {
+  __shared__ double sh[256];
+  double t = 0.0;
+  for (int i = threadIdx.x; i < n; i += 256) t += parts[i];
+  sh[threadIdx.x] = t;
+  for (int m = 128; m > 0; m >>= 1) {
+    __syncthreads();
+    if ((int)threadIdx.x < m) sh[threadIdx.x] += sh[threadIdx.x + m];
   }
+  if (threadIdx.x == 0) *out = sh[0];
 }
 
 __global__ void k_fill_f64(double* p, int64_t n) {
@@ -529,11 +592,24 @@ __global__ __launch_bounds__(256) void k_copy_many(const CopyRec* __restrict__ r
 
 }  // namespace
 
+// f(wall axis, or -1, as a compile-time constant).
+template <class F>
+static void with_wall_axis(const Lattice& L, F f) {
+  if (L.wall_axis == 0) f(std::integral_constant<int, 0>());
+  else if (L.wall_axis == 1) f(std::integral_constant<int, 1>());
+  else if (L.wall_axis == 2) f(std::integral_constant<int, 2>());
+  else f(std::integral_constant<int, -1>());
+}
+
 hipError_t launch_adj_collide(const float* lam1, float* lam0, const float* g0, const float* F,
                               const float* lamu, float* lamF, double* domega_part, unsigned char* mask,
                               double* domega_in_part, const Lattice& L, hipStream_t s) {
-  hipLaunchKernelGGL(k_adj_collide, dim3((unsigned)((L.np + 255) / 256)), dim3(256), 0, s, lam1, lam0,
-                     g0, F, lamu, lamF, domega_part, mask, domega_in_part, L);
+  const int nblk = (int)((L.np + 255) / 256);
+  auto go = [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3(padded_blocks((unsigned)nblk)), dim3(256), 0, s, lam1, lam0, g0, F, lamu, lamF,
+                       domega_part, mask, domega_in_part, L, nblk);
+  };
+  with_wall_axis(L, [&](auto w) { go(k_adj_collide<w.value>); });
   return hipGetLastError();
 }
 
@@ -542,7 +618,7 @@ hipError_t launch_adj_vertex(const Cells& c, const Mesh& m, const Lattice& L, co
                              hipStream_t s) {
   const int64_t n = (int64_t)c.n * m.nv;
   if (n == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_adj_vertex, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, c, m, L, lamX1,
+  hipLaunchKernelGGL(k_adj_vertex, dim3((unsigned)((n * kVertexLanes + 255) / 256)), dim3(256), 0, s, c, m, L, lamX1,
                      macro, lamF, lamFv, lamX0);
   return hipGetLastError();
 }
@@ -562,15 +638,18 @@ hipError_t launch_adj_membrane(const Cells& c, const Mesh& m, const float* lamFv
 
 hipError_t launch_adj_collide_multi(const AdjCollideArgs& a0, const AdjCollideArgs* dev, int n, hipStream_t s) {
   if (n == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_adj_collide_multi, dim3((unsigned)((a0.L.np + 255) / 256), (unsigned)n), dim3(256), 0, s,
-                     dev);
+  const int nblk = (int)((a0.L.np + 255) / 256);
+  auto go = [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3(padded_blocks((unsigned)nblk * n)), dim3(256), 0, s, dev, nblk, n);
+  };
+  with_wall_axis(a0.L, [&](auto w) { go(k_adj_collide_multi<w.value>); });
   return hipGetLastError();
 }
 
 hipError_t launch_adj_vertex_multi(const AdjVertexArgs& a0, const AdjVertexArgs* dev, int n, hipStream_t s) {
   const int64_t nv = (int64_t)a0.C.n * a0.M.nv;
   if (n == 0 || nv == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_adj_vertex_multi, dim3((unsigned)((nv + 255) / 256), (unsigned)n), dim3(256), 0, s, dev);
+  hipLaunchKernelGGL(k_adj_vertex_multi, dim3((unsigned)((nv * kVertexLanes + 255) / 256), (unsigned)n), dim3(256), 0, s, dev);
   return hipGetLastError();
 }
 
@@ -596,7 +675,7 @@ hipError_t launch_loss_seed(const Cells& c, const Mesh& m, const double* targets
 }
 
 hipError_t launch_sum_parts(const double* parts, int n, double* out, hipStream_t s) {
-  hipLaunchKernelGGL(k_sum_parts, dim3(1), dim3(64), 0, s, parts, n, out);
+  hipLaunchKernelGGL(k_sum_parts, dim3(1), dim3(256), 0, s, parts, n, out);
   return hipGetLastError();
 }
 

@@ -117,7 +117,7 @@ __device__ __noinline__ void spread_add_wide(long long* a0, long long* a1, long 
 // tile's list; the thread evaluates its 3 x K axis weights once and adds the
 // contributions of the stencil nodes inside the tile to the LDS accumulator
 // acc[3][512] (zeroed by the caller, synchronised after).
-template <int K, bool LE = false>
+template <int K>
 __device__ inline void spread_tile(const Cells& C, const Mesh& M, const Lattice& L, const Bins& B,
                                    const float* __restrict__ vec, int t, int x0, int y0, int z0,
                                    long long (*acc)[kTile * kTile * kTile]) {
@@ -133,20 +133,14 @@ __device__ inline void spread_tile(const Cells& C, const Mesh& M, const Lattice&
     int lx[K], ly[K], lz[K];
     float wx[K], wy[K], wz[K];
     LeStencil<K> S;
-    if (LE) {
-      le_stencil<K>(L, C.origin[3 * c + 0], o[0], C.origin[3 * c + 2], o[2], x0, S);
-      rotate<K>(S.lxa, S.wxa, rot);
-      rotate<K>(S.lxb, S.wxb, rot);
-    } else {
-      axis_stencil<K>(C.origin[3 * c + 0], o[0], L.nx, L.bc[0] == 1, x0, lx, wx);
-      rotate<K>(lx, wx, rot);
-    }
+    le_stencil<K>(L, C.origin[3 * c + 0], o[0], C.origin[3 * c + 2], o[2], x0, S);
+    rotate<K>(S.lxa, S.wxa, rot);
+    rotate<K>(S.lxb, S.wxb, rot);
     axis_stencil<K>(C.origin[3 * c + 1], o[1], L.ny, L.bc[1] == 1, y0, ly, wy);
     axis_stencil<K>(C.origin[3 * c + 2], o[2], L.nz, L.bc[2] == 1, z0, lz, wz);
     rotate<K>(ly, wy, rot >> 2);
-    // the x stencil of the image z position kz lies in (sheared images only)
+    // the x stencil of the image z position kz lies in
     auto pick_x = [&](int kz) {
-      if (!LE) return;
       const bool a = S.m[kz] == S.ma;
 #pragma unroll
       for (int kx = 0; kx < K; ++kx) {
@@ -257,47 +251,6 @@ __device__ inline void interp_tile(const Cells& C, const Mesh& M, const Lattice&
   }
 }
 
-// Spreading of a vertex field alone (the reverse sweep spreads cotangents
-// with it): writes body * g + the spread field, tile-major (padding slots
-// receive body * g).
-template <int K>
-__device__ __forceinline__ void spread_body(Cells C, Mesh M, Lattice L, Bins B,
-                                            const float* __restrict__ vec, float body, float* __restrict__ F) {
-  __shared__ long long acc[3][kTile * kTile * kTile];
-  const int t = blockIdx.x;
-  int x0, y0, z0;
-  tile_origin(L, t, x0, y0, z0);
-  for (int i = threadIdx.x; i < kTile * kTile * kTile; i += blockDim.x) {
-    acc[0][i] = 0;
-    acc[1][i] = 0;
-    acc[2][i] = 0;
-  }
-  __syncthreads();
-  spread_tile<K>(C, M, L, B, vec, t, x0, y0, z0, acc);
-  __syncthreads();
-  if (threadIdx.x == 0) B.touch_cnt[t] = 0;   // consumed: zero for the next binning
-
-  const int64_t NP = L.np, h0 = (int64_t)t * 512;
-  for (int i = threadIdx.x; i < kTile * kTile * kTile; i += blockDim.x) {
-    F[h0 + i] = body * L.g[0] + (float)((double)acc[0][i] * kFixInv);
-    F[NP + h0 + i] = body * L.g[1] + (float)((double)acc[1][i] * kFixInv);
-    F[2 * NP + h0 + i] = body * L.g[2] + (float)((double)acc[2][i] * kFixInv);
-  }
-}
-
-template <int K>
-__global__ __launch_bounds__(256) void k_spread(Cells C, Mesh M, Lattice L, Bins B,
-                                                const float* __restrict__ vec, float body,
-                                                float* __restrict__ F) {
-  spread_body<K>(C, M, L, B, vec, body, F);
-}
-
-template <int K>
-__global__ __launch_bounds__(256) void k_spread_multi(const SpreadArgs* __restrict__ many) {
-  const SpreadArgs& a = launch_record(many, blockIdx.y);
-  spread_body<K>(a.C, a.M, a.L, a.B, a.vec, a.body, a.F);
-}
-
 // Which tile block b works on.  Work-groups go to the 8 XCDs round-robin by
 // block id; each XCD gets one contiguous range of tiles, walked in order, so
 // the neighbours a tile pulls boundary populations from were mostly just
@@ -336,7 +289,8 @@ __host__ __device__ inline int tile_grid(const Lattice& L) { return ((L.ntiles +
 // With sheared images (two or more tiles along z) the nodes of one entry
 // all lie in one image, so an entry is staged at its x as seen from that
 // image and walks its nodes like any other; the image index is kept for the
-// image's velocity.  Its forces accumulate as 2^-40 fixed-point int64.
+// image's velocity.  Its forces accumulate as 2^-40 fixed-point int64, as
+// do the reverse sweep's cotangents.
 namespace srt {
 
 // Records staged at once.  With 32 bytes each the work-group's LDS allows six
@@ -354,20 +308,20 @@ constexpr int kKeys = 64;     // box shapes: 1..4 in-tile nodes on each axis
 constexpr int kRow = 9, kPlane = 77, kNodes = 8 * kPlane;
 __device__ __forceinline__ int node_at(int i) { return (i >> 6) * kPlane + ((i >> 3) & 7) * kRow + (i & 7); }
 
-template <bool LE>
+template <bool I64>
 struct Smem {
-  // spread accumulator: int32 at the tile's scale (sheared images: 2^-40 int64)
-  typename std::conditional<LE, long long, int>::type acc[3][kNodes];
+  // spread accumulator: int32 at the tile's scale, or 2^-40 int64
+  typename std::conditional<I64, long long, int>::type acc[3][kNodes];
   float4 pos[kStage];       // fractions x, y, z; axis runs (bits)
   float4 force[kStage];     // force x, y, z; entry code (vertex * 32 + slot, bits)
   int cnt[kKeys];           // records per box shape, then the first record of each shape
   unsigned fmax;            // largest force component magnitude (float bits)
   int fsum;                 // sum of the entries' largest components, in units of fmax 2^-bexp
-  int image[LE ? kStage : 1];   // image index of the record's nodes
+  int image[I64 ? kStage : 1];   // image index of the record's nodes
   // The velocity takes the accumulator's place, each node's in the slots of
   // its own sums, so the thread that owns a node needs no other's data.
   __device__ __forceinline__ void put_u(int i, float x, float y, float z) {
-    if (LE) {
+    if (I64) {
       reinterpret_cast<float2*>(acc[0])[i] = make_float2(x, y);
       reinterpret_cast<float2*>(acc[1])[i].x = z;
     } else {
@@ -377,7 +331,7 @@ struct Smem {
     }
   }
   __device__ __forceinline__ float3 get_u(int i) const {
-    if (LE) {
+    if (I64) {
       const float2 a = reinterpret_cast<const float2*>(acc[0])[i];
       return make_float3(a.x, a.y, reinterpret_cast<const float2*>(acc[1])[i].x);
     }
@@ -565,10 +519,11 @@ __device__ __forceinline__ int first_chunk(int ne) { return ne - (ne - 1) / kSta
 // records ordered by box shape; with_force also stages the forces, and with
 // bound as well the force bound of these entries (S.fmax, S.fsum: the whole
 // tile's when they are all staged at once).  Ends synchronised.
-template <int K, bool LE>
-__device__ __forceinline__ void stage(const Cells& C, const Mesh& M, const Lattice& L, const Bins& B, int t,
+template <int K, bool LE, bool I64>
+__device__ __forceinline__ void stage(const Cells& C, const Mesh& M, const Lattice& L, const Bins& B,
+                                      const float* __restrict__ vec, int t,
                              int x0, int y0, int z0, int e0, int m, bool with_force, bool bound,
-                             Smem<LE>& S) {
+                             Smem<I64>& S) {
   for (int i = threadIdx.x; i < kKeys; i += blockDim.x) S.cnt[i] = 0;
   lds_barrier();
   constexpr int R = kPerThread;
@@ -605,7 +560,7 @@ __device__ __forceinline__ void stage(const Cells& C, const Mesh& M, const Latti
       pos[h] = make_float4(ox - fx, oy - fy, oz - fz, __uint_as_float(rx | (ry << 8) | (rz << 16)));
       force[h].w = __int_as_float(code);
       if (with_force) {
-        const float* fv = C.force + (int64_t)v * 3;
+        const float* fv = vec + (int64_t)v * 3;
         force[h].x = fv[0];
         force[h].y = fv[1];
         force[h].z = fv[2];
@@ -658,14 +613,14 @@ __device__ __forceinline__ void stage(const Cells& C, const Mesh& M, const Latti
 // the square root of the contributions times half a unit; the unit grows
 // with the tile's force bound, i.e. with its entries, so crowded tiles
 // (more than kRoundAbove entries) round.
-// The int64 sums of sheared images truncate at 2^40 (scale): forces of 2^-9
+// The int64 sums truncate at 2^40 (scale): forces of 2^-9
 // and more take the full-range conversion (WIDE), a truncation as well, so
 // which of the two an entry takes never changes an integer.
 constexpr int kRoundAbove = 1024;
-template <int K, bool RN, bool WIDE, bool SMALL, bool LE>
-__device__ __forceinline__ void spread_entries(int m, const Lattice& L, float scale, Smem<LE>& S) {
+template <int K, bool RN, bool WIDE, bool SMALL, bool I64>
+__device__ __forceinline__ void spread_entries(int m, const Lattice& L, float scale, Smem<I64>& S) {
   auto add = [&](int comp, int li, float q) {
-    if (LE) {
+    if (I64) {
       const long long n = WIDE ? (long long)q : (long long)(int)q;
       atomicAdd(reinterpret_cast<unsigned long long*>(&S.acc[comp][li]), (unsigned long long)n);
     } else {
@@ -708,9 +663,9 @@ __device__ __forceinline__ void spread_entries(int m, const Lattice& L, float sc
   }
 }
 
-template <int K, bool SMALL, bool LE>
-__device__ __forceinline__ void spread(int m, const Lattice& L, int ne, int kexp, Smem<LE>& S) {
-  if constexpr (LE) {
+template <int K, bool SMALL, bool I64>
+__device__ __forceinline__ void spread(int m, const Lattice& L, int ne, int kexp, Smem<I64>& S) {
+  if constexpr (I64) {
     bool wide = false;   // the wave's choice: any of its forces
     for (int i = threadIdx.x; i < m; i += kThreads) {
       const float4 f = S.force[i];
@@ -773,6 +728,58 @@ __device__ __forceinline__ void interp(int m, const Lattice& L, const Smem<LE>& 
 }
 
 }  // namespace srt
+
+// Spreading of a vertex field alone (the reverse sweep spreads cotangents
+// with it): writes body * g + the spread field, tile-major (padding slots
+// receive body * g).  Its entries are staged and sorted like the lattice
+// pass's, in int64 sums: one box of 32^3 14 us, 24.5 with a thread per unsorted
+// entry testing every node; 64 boxes of 48^3 53 and 61.
+template <int K, class CT, class MT, class LT, class BT>
+__device__ __forceinline__ void spread_body(CT C, MT M, LT L, BT B, const float* __restrict__ vec, float body,
+                                            float* __restrict__ F) {
+  __shared__ srt::Smem<true> S;
+  const int t = blockIdx.x;
+  int x0, y0, z0;
+  tile_origin(L, t, x0, y0, z0);
+  for (int i = threadIdx.x; i < srt::kNodes; i += blockDim.x) {
+    S.acc[0][i] = 0;
+    S.acc[1][i] = 0;
+    S.acc[2][i] = 0;
+  }
+  const int ne = min(B.touch_cnt[t], B.cap);
+  lds_barrier();
+  const bool small = min(L.nx, min(L.ny, L.nz)) <= srt::kSmall;
+  for (int e0 = 0; e0 < ne; e0 += srt::kStage) {
+    const int m = min(ne - e0, srt::kStage);
+    srt::stage<K, false>(C, M, L, B, vec, t, x0, y0, z0, e0, m, true, false, S);
+    if (small) srt::spread<K, true>(m, L, ne, 0, S);
+    else srt::spread<K, false>(m, L, ne, 0, S);
+    lds_barrier();
+  }
+  // every thread has used the count: leave it zero for the next binning
+  if (ne > 0 && threadIdx.x == 0) B.touch_cnt[t] = 0;
+
+  const int64_t NP = L.np, h0 = (int64_t)t * 512;
+  for (int i = threadIdx.x; i < kTile * kTile * kTile; i += blockDim.x) {
+    const int li = srt::node_at(i);
+    F[h0 + i] = body * L.g[0] + (float)((double)S.acc[0][li] * kFixInv);
+    F[NP + h0 + i] = body * L.g[1] + (float)((double)S.acc[1][li] * kFixInv);
+    F[2 * NP + h0 + i] = body * L.g[2] + (float)((double)S.acc[2][li] * kFixInv);
+  }
+}
+
+template <int K>
+__global__ __launch_bounds__(256) void k_spread(Cells C, Mesh M, Lattice L, Bins B,
+                                                const float* __restrict__ vec, float body,
+                                                float* __restrict__ F) {
+  spread_body<K, Cells, Mesh, Lattice, Bins>(C, M, L, B, vec, body, F);
+}
+
+template <int K>
+__global__ __launch_bounds__(256) void k_spread_multi(const SpreadArgs* __restrict__ many) {
+  const SpreadArgs& a = launch_record(many, blockIdx.y);
+  spread_body<K, const Cells&, const Mesh&, const Lattice&, const Bins&>(a.C, a.M, a.L, a.B, a.vec, a.body, a.F);
+}
 
 constexpr int kNoWall = -1, kAnyWall = 3;
 
@@ -841,7 +848,7 @@ __device__ __forceinline__ void tile_step_sorted_body(CT C, MT M, LT L, BT B,
     if constexpr (!LE)
       if (!bound) srt::force_bound(C, B, t, ne, S);
     for (int e0 = 0, m = srt::first_chunk(ne); e0 < ne; e0 += m, m = srt::kStage) {
-      srt::stage<K, LE>(C, M, L, B, t, x0, y0, z0, e0, m, true, bound, S);
+      srt::stage<K, LE>(C, M, L, B, C.force, t, x0, y0, z0, e0, m, true, bound, S);
       if (!LE && e0 == 0)
         kexp = srt::fix_exponent(S.fsum, __uint_as_float(S.fmax), srt::max_node_weight(L), B.bexp);
       if (small) srt::spread<K, true>(m, L, ne, kexp, S);
@@ -947,7 +954,7 @@ __device__ __forceinline__ void tile_step_sorted_body(CT C, MT M, LT L, BT B,
     interp(srt::kStage);
     lds_barrier();
     for (int e0 = 0, m = srt::first_chunk(ne); e0 < ne - srt::kStage; e0 += m, m = srt::kStage) {
-      srt::stage<K, LE>(C, M, L, B, t, x0, y0, z0, e0, m, false, false, S);
+      srt::stage<K, LE>(C, M, L, B, C.force, t, x0, y0, z0, e0, m, false, false, S);
       interp(m);
       lds_barrier();
     }
@@ -1012,7 +1019,7 @@ __global__ __launch_bounds__(256) void k_tile_step_le_thin(Cells C, Mesh M, Latt
     acc[2][i] = 0;
   }
   __syncthreads();
-  if (C.n > 0) spread_tile<K, true>(C, M, L, B, C.force, t, x0, y0, z0, acc);
+  if (C.n > 0) spread_tile<K>(C, M, L, B, C.force, t, x0, y0, z0, acc);
   __syncthreads();
 
   const int64_t NP = L.np, h0 = (int64_t)t * 512;

@@ -323,3 +323,32 @@ def test_multi_box_adjoint_equals_single_box():
     assert np.all(np.isfinite(loss2)) and np.all(np.isfinite(Simulation.adj_multi_backward(sims)))
     for s in sims:
         s.close()
+
+
+@pytest.mark.parametrize("shape,wall", [((20, 18, 21), 0), ((17, 24, 10), 1), ((9, 20, 24), -1)])
+def test_adjoint_other_axes_and_ragged_sides(shape, wall):
+    """Walls on the other axes, sides that leave partial tiles and a periodic
+    side whose seam lies in the first tile: gradient against the oracle's
+    complex step, with the bar of the cubes above."""
+    rng = np.random.default_rng(31)
+    rest64, tri = rbc_mesh()
+    bc, u = [0, 0, 0], [0.0, 0.0, 0.0]
+    if wall >= 0:
+        bc[wall] = 1
+        u[(wall + 1) % 3] = 0.01
+    lat = Lattice(*shape, bc=tuple(bc), tau=0.9, wall_u_lo=tuple(-x for x in u), wall_u_hi=tuple(u))
+    centre = (np.array(shape) - 1) / 2.0 + rng.uniform(-0.5, 0.5, 3)
+    if wall == 1:   # the flat axis of the cell across the narrow box
+        centre[1] = 11.0
+    cells = place_cells(rest64, centre[None], small_rotation(rng, 5.0)[None], K_REF[None],
+                        traction=[[3e-3, 0.0, 0.0]])
+    targets = np.array([16.0 * 1.2, 16.0 * 0.9])
+    n = 16
+    _, g, _ = _device_grad(lat, rest64.astype(np.float32), tri, cells, targets, n, 8)
+    k = cells.k[0].astype(np.float64)
+    g_cs = oadj.cs_gradient(lat, rest64.astype(np.float32), tri, cells.positions64()[0], k, cells.traction[0],
+                            lat.tau, n, targets)
+    p = np.concatenate([k, [lat.tau]])
+    norm = np.linalg.norm(p * (g - g_cs)) / np.linalg.norm(p * g_cs)
+    print(shape, wall, "p.g", p * g, "complex step", p * g_cs, "norm", norm, flush=True)
+    assert norm <= 1e-4
