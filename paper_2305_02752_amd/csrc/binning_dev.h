@@ -133,9 +133,9 @@ __host__ __device__ inline int slot_lds_per_vertex(int max_touch) { return 3 * m
 constexpr int kSpan = 6;   // tiles per axis of the direct table (kSpan^3 <= kHash)
 static_assert(kSpan * kSpan * kSpan <= kHash, "direct table exceeds the LDS table");
 
-__device__ inline int wave_min_i(int v) {
+__device__ inline int wave_max_i(int v) {
 #pragma unroll
-  for (int d = kWave / 2; d > 0; d >>= 1) v = min(v, __shfl_xor(v, d));
+  for (int d = kWave / 2; d > 0; d >>= 1) v = max(v, __shfl_xor(v, d));
   return v;
 }
 
@@ -160,7 +160,7 @@ __device__ inline void bin_cell(const Cells& C, const Mesh& M, const Lattice& L,
       }
 #pragma unroll
     for (int q = 0; q < 6; ++q) {
-      const int w = -wave_min_i(-e[q]);
+      const int w = wave_max_i(e[q]);   // (a lane without vertices holds INT_MIN, which has no negative)
       if ((tid & (kWave - 1)) == 0) atomicMax(&keys[250 + q], w);
     }
   }
@@ -185,6 +185,7 @@ __device__ inline void bin_cell(const Cells& C, const Mesh& M, const Lattice& L,
         t_lo[d] = wrap(lo, n[d]) / kTile;
         const int t_hi = wrap(hi, n[d]) / kTile;
         span = (t_hi - t_lo[d] + T[d]) % T[d] + 1;
+        if (span == 1 && hi - lo >= kTile) span = T[d];   // round the axis, back into the first tile
       }
       direct = direct && span <= kSpan;
     }
@@ -252,8 +253,13 @@ __device__ inline void bin_cell(const Cells& C, const Mesh& M, const Lattice& L,
             rx += rx < 0 ? T[0] : 0;
             ry += ry < 0 ? T[1] : 0;
             rz += rz < 0 ? T[2] : 0;
-            h = (rz * kSpan + ry) * kSpan + rx;
-            if (keys[h] != tile) keys[h] = tile;   // every writer stores the same tile
+            // past the box: only offsets beyond the integers, whose extent means nothing
+            if (max(rx, max(ry, rz)) >= kSpan) {
+              h = kHash;
+            } else {
+              h = (rz * kSpan + ry) * kSpan + rx;
+              if (keys[h] != tile) keys[h] = tile;   // every writer stores the same tile
+            }
           } else {
             h = hash_slot(tile);
           }

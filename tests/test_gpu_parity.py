@@ -518,3 +518,39 @@ def test_lattice_pass_small_axes_and_chunks(n, walls, kernel, n_cells):
     print(n, walls, kernel, n_cells, errs, flush=True)
     for k, e in errs.items():
         assert e <= TOL_STEP, (k, e)
+
+
+@pytest.mark.parametrize("case", ["low", "high", "round"])
+def test_binning_bit_exact_at_the_table_edges(case):
+    """The last vertices of the mesh alone reach one tile further than the
+    others on every axis, on a lattice of more tiles than the direct table
+    spans; and a cell that reaches round an axis of 7 tiles back into its
+    first one."""
+    from types import SimpleNamespace
+    from workloads import rbc_mesh
+    rest64, tri = rbc_mesh()
+    scale, n = (2.8, (50, 64, 64)) if case == "round" else (1.0, (80, 72, 64))
+    lat = Lattice(*n)
+    cells = place_cells(scale * rest64, np.array(n, dtype=float)[None] / 2, np.eye(3)[None], K_REF[None])
+    x = cells.origin[0] + cells.offsets[0].astype(np.float64)
+    if case == "round":   # first stencil node 7, last one past n + 1
+        cells.offsets[0, :, 0] += np.float32(8.3 - x[:, 0].min())
+        x = cells.origin[0] + cells.offsets[0].astype(np.float64)
+        lo, hi = int(np.floor(x[:, 0].min())) - 1, int(np.floor(x[:, 0].max())) + 2
+        assert lo // 8 == 0 and hi - n[0] >= 0 and (hi - n[0]) // 8 == 0 and hi - lo + 1 < n[0]
+    else:   # the others' first (last) stencil node is the first (last) of a tile
+        s = 1.0 if case == "low" else -1.0
+        ext = x.min(0) if case == "low" else x.max(0)
+        goal = np.floor(ext / 8) * 8 + (9.5 if case == "low" else 5.5)
+        cells.offsets[0] += (goal - ext).astype(np.float32)
+        far = cells.offsets[0].min(0) if case == "low" else cells.offsets[0].max(0)
+        cells.offsets[0, -2:] = far - np.float32(2.0 * s)
+    sim = make_sim(SimpleNamespace(lattice=lat, rest_pos=(scale * rest64).astype(np.float32), tri=tri, cells=cells),
+                   cells)
+    o, off, _ = sim.read_vertices()
+    owner, tptr, touch, cptr, clist = sim.read_bins()
+    ow, _, _, cptr_r, clist_r = binning.bins(o, off, n, lat.bc)
+    tptr_r, touch_r = binning.touch_lists(o, off, n, lat.bc, 4)
+    assert np.array_equal(owner, ow)
+    assert np.array_equal(cptr, cptr_r) and np.array_equal(clist, clist_r)
+    assert np.array_equal(tptr, tptr_r) and np.array_equal(touch, touch_r)
