@@ -58,8 +58,9 @@ __device__ inline int bin_axis(const PackGeom& G, int a, float x) {
   return min(max(b, 0), G.nb[a] - 1);
 }
 
+// (within half a period the nearest image is d itself: no division)
 __device__ inline float min_image(const PackGeom& G, int a, float d) {
-  return G.per[a] ? d - G.L[a] * rintf(d / G.L[a]) : d;
+  return G.per[a] && !(fabsf(d) < 0.49f * G.L[a]) ? d - G.L[a] * rintf(d / G.L[a]) : d;
 }
 
 // The frames of a pair, with dd = r_a - r_b (minimum image); R row-major
@@ -178,6 +179,10 @@ __device__ inline float lane_f(float v, int src) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), src));
 }
 
+// a / m for 0 <= a < 2^16 and small m (inv: its reciprocal): (a + 1/2) / m is
+// no nearer than 1 / 2m to a whole number.
+__device__ inline int div_m(int a, float inv) { return (int)(((float)a + 0.5f) * inv); }
+
 // One iteration for every ellipsoid: pushes from the positions rin, written
 // to rout when move is set; per ellipsoid, the fixed-point overlapping
 // volume with higher-indexed partners (vol) and their number (pairs).
@@ -195,7 +200,7 @@ __global__ __launch_bounds__(kPackThreads) void k_pack_iter(
   __syncthreads();
   const float inv_m = 1.f / (float)G.m;
   for (int k = threadIdx.x; k < G.m * G.m * G.m; k += blockDim.x) {
-    const int a = k % G.m, b = (k / G.m) % G.m, c = k / (G.m * G.m);
+    const int q = div_m(k, inv_m), c = div_m(q, inv_m), a = k - q * G.m, b = q - c * G.m;
     // (2a + 1) / m - 1, exact for m a power of two
     const float ux = (float)(2 * a + 1) * inv_m - 1.f;
     const float uy = (float)(2 * b + 1) * inv_m - 1.f;
@@ -234,7 +239,9 @@ __global__ __launch_bounds__(kPackThreads) void k_pack_iter(
   const int nbn = nz * ny * nx;
   int my_bin = 0, my_cnt = 0;
   if (lane < nbn) {
-    const int a = lane / (ny * nx), b = (lane / nx) % ny, c = lane % nx;
+    // (nx, ny in 1..3)
+    const float inv_x = 1.f / (float)nx;
+    const int q = div_m(lane, inv_x), a = div_m(q, 1.f / (float)ny), b = q - a * ny, c = lane - q * nx;
     my_bin = (Bz[a] * G.nb[1] + By[b]) * G.nb[0] + Bx[c];
     my_cnt = min(cnt[my_bin], G.cap);
   }
@@ -253,7 +260,7 @@ __global__ __launch_bounds__(kPackThreads) void k_pack_iter(
     const int k = base + lane;
     // owning bin of candidate k: the last bin whose offset is <= k
     int owner = 0;
-    for (int l = 1; l < nbn; ++l) owner = __shfl(excl, l) <= k ? l : owner;
+    for (int l = 1; l < nbn; ++l) owner = __builtin_amdgcn_readlane(excl, l) <= k ? l : owner;
     const int bin = __shfl(my_bin, owner);
     const int slot = k - __shfl(excl, owner);
     bool pass = false;
