@@ -61,6 +61,15 @@ __device__ inline void axis_local(int origin, float x, int n, bool wall, int t0,
   }
 }
 
+// a[k] of a small array in registers.
+template <int K, class T>
+__device__ __forceinline__ T pick(const T (&a)[K], int k) {
+  T r = a[0];
+#pragma unroll
+  for (int q = 1; q < K; ++q) r = k == q ? a[q] : r;
+  return r;
+}
+
 // The wait polls with relaxed loads and takes one acquire fence when it
 // ends: an acquire on every poll would invalidate the XCD's L2 each time,
 // which the other work-groups of the XCD, still streaming, pay for.
@@ -151,11 +160,53 @@ __device__ inline bool stencil_meets(int base, int a, int h, int n, bool wall) {
   return range_meets(base, base + K - 1, a, h, n, wall);
 }
 
+// Vertices of [v0, v1) whose stencils meet the tile's rows, listed in LDS
+// (any order: what they add up are integers); *n is their number.  Ends
+// synchronised, as the caller has to begin.
+template <int K>
+__device__ __forceinline__ void list_vertices(const BoxDesc& B, const float* __restrict__ off, const int* o3,
+                                              int v0, int v1, int y0, int hy, int z0, int hz, int* list, int* n,
+                                              int tid, int nthr) {
+  const int sh = K == 4 ? 1 : 0;
+  if (tid == 0) *n = 0;
+  __syncthreads();
+  for (int b = v0; b < v1; b += nthr) {
+    const int v = b + tid;
+    const bool meets = v < v1 &&
+                       stencil_meets<K>(o3[1] + (int)floorf(off[3 * v + 1]) - sh, y0, hy, B.ny, B.bc[1] == 1) &&
+                       stencil_meets<K>(o3[2] + (int)floorf(off[3 * v + 2]) - sh, z0, hz, B.nz, B.bc[2] == 1);
+    const unsigned long long m = __ballot(meets);
+    if (m == 0) continue;
+    int at = 0;
+    if ((tid & (kWave - 1)) == 0) at = atomicAdd(n, (int)__popcll(m));
+    at = __builtin_amdgcn_readfirstlane(at);
+    if (meets) list[at + __popcll(m & ((1ull << (tid & (kWave - 1))) - 1))] = v;
+  }
+  __syncthreads();
+}
+
+// Sum over the K lanes of a vertex (2 or 4, neighbours).
+template <int CTRL>
+__device__ __forceinline__ long long lane_add(long long v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(v >> 32), CTRL, 0xF, 0xF, false);
+  return v + (((long long)hi << 32) | (unsigned)lo);
+}
+template <int K>
+__device__ __forceinline__ long long vertex_sum(long long v) {
+  v = lane_add<0xB1>(v);               // lane xor 1
+  return K == 4 ? lane_add<0x4E>(v) : v;   // lane xor 2
+}
+
+// Spread and interpolation take the vertices that meet the tile from a list,
+// K lanes per vertex (one z layer of its stencil each).  Bound by the chain
+// of phases a work-group runs per step; with a lane per vertex of the cell a
+// wave walked 64 nodes for the few of its lanes that met the tile: @BATCH@
 template <int K>
 __device__ void box_tile(const Batch& V, const BoxDesc& B, int box, int t, const float* __restrict__ gin,
                          float* __restrict__ gout, const float* __restrict__ off,
                          const float* __restrict__ force, const int* o3, long long* facc, float4* su,
-                         int tid, int nthr) {
+                         int* s_n, int tid, int nthr) {
   const int nv = V.M.nv;
   const int y0 = (t % B.nty) * B.ty, z0 = (t / B.nty) * B.tz;
   const int hy = min(B.ty, B.ny - y0), hz = min(B.tz, B.nz - z0);
@@ -165,28 +216,29 @@ __device__ void box_tile(const Batch& V, const BoxDesc& B, int box, int t, const
                     range_meets(bb[4], bb[5], z0, hz, B.nz, B.bc[2] == 1);
   if (near) {
     for (int i = tid; i < 3 * nsite; i += nthr) facc[i] = 0;
-    __syncthreads();
-    for (int v = tid; v < nv; v += nthr) {
-      const float py = off[3 * v + 1], pz = off[3 * v + 2];
-      const int sh = K == 4 ? 1 : 0;
-      if (!stencil_meets<K>(o3[1] + (int)floorf(py) - sh, y0, hy, B.ny, B.bc[1] == 1) ||
-          !stencil_meets<K>(o3[2] + (int)floorf(pz) - sh, z0, hz, B.nz, B.bc[2] == 1))
-        continue;
-      int lx[K], ly[K], lz[K];
-      float wx[K], wy[K], wz[K];
-      axis_local<K>(o3[1], py, B.ny, B.bc[1] == 1, y0, hy, ly, wy);
-      axis_local<K>(o3[2], pz, B.nz, B.bc[2] == 1, z0, hz, lz, wz);
-      axis_local<K>(o3[0], off[3 * v], B.nx, B.bc[0] == 1, 0, B.nx, lx, wx);
-      const float fx = force[3 * v] * kFixScaleF, fy = force[3 * v + 1] * kFixScaleF,
-                  fz = force[3 * v + 2] * kFixScaleF;
-#pragma unroll
-      for (int kz = 0; kz < K; ++kz) {
-        if (lz[kz] < 0) continue;
+    // the list lies in the velocities' place, written only after the spread
+    int* list = reinterpret_cast<int*>(su);
+    const int room = 4 * nsite;
+    for (int v0 = 0; v0 < nv; v0 += room) {
+      list_vertices<K>(B, off, o3, v0, min(v0 + room, nv), y0, hy, z0, hz, list, s_n, tid, nthr);
+      const int nu = *s_n * K;
+      for (int u = tid; u < nu; u += nthr) {
+        const int v = list[u / K], kz = u % K;
+        int lx[K], ly[K], lz[K];
+        float wx[K], wy[K], wz[K];
+        axis_local<K>(o3[2], off[3 * v + 2], B.nz, B.bc[2] == 1, z0, hz, lz, wz);
+        const int z = pick<K>(lz, kz);
+        if (z < 0) continue;
+        const float wzk = pick<K>(wz, kz);
+        axis_local<K>(o3[1], off[3 * v + 1], B.ny, B.bc[1] == 1, y0, hy, ly, wy);
+        axis_local<K>(o3[0], off[3 * v], B.nx, B.bc[0] == 1, 0, B.nx, lx, wx);
+        const float fx = force[3 * v] * kFixScaleF, fy = force[3 * v + 1] * kFixScaleF,
+                    fz = force[3 * v + 2] * kFixScaleF;
 #pragma unroll
         for (int ky = 0; ky < K; ++ky) {
           if (ly[ky] < 0) continue;
-          const float wzy = wz[kz] * wy[ky];
-          const int row = (lz[kz] * hy + ly[ky]) * B.nx;
+          const float wzy = wzk * wy[ky];
+          const int row = (z * hy + ly[ky]) * B.nx;
 #pragma unroll
           for (int kx = 0; kx < K; ++kx) {
             if (lx[kx] < 0) continue;
@@ -196,8 +248,8 @@ __device__ void box_tile(const Batch& V, const BoxDesc& B, int box, int t, const
           }
         }
       }
+      __syncthreads();
     }
-    __syncthreads();
   }
   const int64_t N = B.n;
   const float* gi = gin + B.pop_off;
@@ -209,9 +261,10 @@ __device__ void box_tile(const Batch& V, const BoxDesc& B, int box, int t, const
     W.lo[d] = B.ulo[d];
     W.hi[d] = B.uhi[d];
   }
+  const float rnx = __builtin_amdgcn_rcpf((float)B.nx), rhy = __builtin_amdgcn_rcpf((float)hy);
   for (int i = tid; i < nsite; i += nthr) {
-    const int x = i % B.nx, r = i / B.nx;
-    const int y = y0 + r % hy, z = z0 + r / hy;
+    const int r = div_small(i, B.nx, rnx), q = div_small(r, hy, rhy);
+    const int x = i - r * B.nx, y = y0 + r - q * hy, z = z0 + q;
     const int64_t s = ((int64_t)z * B.ny + y) * B.nx + x;
     float g[kQ];
 #pragma unroll
@@ -244,28 +297,28 @@ __device__ void box_tile(const Batch& V, const BoxDesc& B, int box, int t, const
   if (near) {
     __syncthreads();
     long long* U = V.uacc + (int64_t)box * nv * 3;
-    for (int v = tid; v < nv; v += nthr) {
-      const float py = off[3 * v + 1], pz = off[3 * v + 2];
-      const int sh = K == 4 ? 1 : 0;
-      if (!stencil_meets<K>(o3[1] + (int)floorf(py) - sh, y0, hy, B.ny, B.bc[1] == 1) ||
-          !stencil_meets<K>(o3[2] + (int)floorf(pz) - sh, z0, hz, B.nz, B.bc[2] == 1))
-        continue;
-      int lx[K], ly[K], lz[K];
-      float wx[K], wy[K], wz[K];
-      axis_local<K>(o3[1], py, B.ny, B.bc[1] == 1, y0, hy, ly, wy);
-      axis_local<K>(o3[2], pz, B.nz, B.bc[2] == 1, z0, hz, lz, wz);
-      axis_local<K>(o3[0], off[3 * v], B.nx, B.bc[0] == 1, 0, B.nx, lx, wx);
-      // every node contribution is rounded to fixed point on its own, so the
-      // vertex velocity does not depend on how nodes are grouped into tiles
-      long long sx = 0, sy = 0, sz = 0;
-#pragma unroll
-      for (int kz = 0; kz < K; ++kz) {
-        if (lz[kz] < 0) continue;
+    int* list = reinterpret_cast<int*>(facc);   // the force sums have been read
+    const int room = 6 * nsite;
+    for (int v0 = 0; v0 < nv; v0 += room) {
+      list_vertices<K>(B, off, o3, v0, min(v0 + room, nv), y0, hy, z0, hz, list, s_n, tid, nthr);
+      const int nu = *s_n * K;
+      for (int u = tid; u < nu; u += nthr) {
+        const int v = list[u / K], kz = u % K;
+        int lx[K], ly[K], lz[K];
+        float wx[K], wy[K], wz[K];
+        axis_local<K>(o3[2], off[3 * v + 2], B.nz, B.bc[2] == 1, z0, hz, lz, wz);
+        axis_local<K>(o3[1], off[3 * v + 1], B.ny, B.bc[1] == 1, y0, hy, ly, wy);
+        axis_local<K>(o3[0], off[3 * v], B.nx, B.bc[0] == 1, 0, B.nx, lx, wx);
+        const int z = pick<K>(lz, kz);
+        const float wzk = pick<K>(wz, kz);
+        // every node contribution is rounded to fixed point on its own, so the
+        // vertex velocity does not depend on how nodes are grouped into tiles
+        long long sx = 0, sy = 0, sz = 0;
 #pragma unroll
         for (int ky = 0; ky < K; ++ky) {
-          if (ly[ky] < 0) continue;
-          const float wzy = wz[kz] * wy[ky] * kFixScaleF;
-          const int row = (lz[kz] * hy + ly[ky]) * B.nx;
+          if (z < 0 || ly[ky] < 0) continue;
+          const float wzy = wzk * wy[ky] * kFixScaleF;
+          const int row = (z * hy + ly[ky]) * B.nx;
 #pragma unroll
           for (int kx = 0; kx < K; ++kx) {
             if (lx[kx] < 0) continue;
@@ -276,12 +329,17 @@ __device__ void box_tile(const Batch& V, const BoxDesc& B, int box, int t, const
             sz += __float2ll_rn(w * q.z);
           }
         }
+        sx = vertex_sum<K>(sx);
+        sy = vertex_sum<K>(sy);
+        sz = vertex_sum<K>(sz);
+        if (kz == 0) {
+          atomicAdd((unsigned long long*)&U[3 * v], (unsigned long long)sx);
+          atomicAdd((unsigned long long*)&U[3 * v + 1], (unsigned long long)sy);
+          atomicAdd((unsigned long long*)&U[3 * v + 2], (unsigned long long)sz);
+        }
       }
-      atomicAdd((unsigned long long*)&U[3 * v], (unsigned long long)sx);
-      atomicAdd((unsigned long long*)&U[3 * v + 1], (unsigned long long)sy);
-      atomicAdd((unsigned long long*)&U[3 * v + 2], (unsigned long long)sz);
+      __syncthreads();
     }
-    __syncthreads();
   }
 }
 
@@ -335,7 +393,7 @@ __device__ void box_advect(const Batch& V, const BoxDesc& B, int box, const int*
 template <int K>
 __global__ void k_batch(Batch V, int nsteps) {
   extern __shared__ __align__(16) unsigned char lds[];
-  __shared__ int s_ok;
+  __shared__ int s_ok, s_n;
   __shared__ double red[2 * 16];
   __shared__ float fred[6 * 16];
   const int4 me = V.wg[blockIdx.x];
@@ -374,7 +432,7 @@ __global__ void k_batch(Batch V, int nsteps) {
     const float* gin = odd ? V.pops1 : V.pops0;
     float* gout = odd ? V.pops0 : V.pops1;
     for (int t = rank; t < ntiles; t += members)
-      box_tile<K>(V, B, box, t, gin, gout, off, force, o3, facc, su, tid, nthr);
+      box_tile<K>(V, B, box, t, gin, gout, off, force, o3, facc, su, &s_n, tid, nthr);
     if (!group_barrier(ctr, members, epoch, V.flags + 1, V.spin_limit, &s_ok)) return;
     if (rank == 0 && V.has_cells) {
       box_advect<K>(V, B, box, o3, tid, nthr);
