@@ -77,39 +77,6 @@ __device__ inline void collide(float (&g)[kQ], float fx, float fy, float fz, flo
   }
 }
 
-// Where population i leaving node (x, y, z) lands.  Periodic axes wrap; on
-// the wall axis a population leaving the fluid returns to its own node in
-// the opposite direction (half-way bounce-back), and *dw receives Ladd's
-// moving-wall correction -6 w_i rho (e_i . u_wall) to add to it.
-// Returns the destination population index; *dst the destination node.
-struct Walls {
-  int axis;                 // -1: none
-  float lo[3], hi[3];       // lower / upper wall velocity
-};
-
-__device__ inline int stream_target(int i, int x, int y, int z, int nx, int ny, int nz,
-                                    const Walls& W, float rho, int64_t* dst, float* dw) {
-  const int wall_axis = W.axis;
-  int xt = x + cx[i], yt = y + cy[i], zt = z + cz[i];
-  int crossed = 0;  // 0 none, 1 lower wall, 2 upper wall
-  if (wall_axis == 0 && cx[i] != 0) crossed = xt < 0 ? 1 : (xt >= nx ? 2 : 0);
-  if (wall_axis == 1 && cy[i] != 0) crossed = yt < 0 ? 1 : (yt >= ny ? 2 : 0);
-  if (wall_axis == 2 && cz[i] != 0) crossed = zt < 0 ? 1 : (zt >= nz ? 2 : 0);
-  if (crossed) {
-    const float uw = crossed == 1 ? cx[i] * W.lo[0] + cy[i] * W.lo[1] + cz[i] * W.lo[2]
-                                  : cx[i] * W.hi[0] + cy[i] * W.hi[1] + cz[i] * W.hi[2];
-    *dw = -2.f * kq[i] * rho * uw;
-    *dst = ((int64_t)z * ny + y) * nx + x;
-    return opp[i];
-  }
-  xt = xt < 0 ? xt + nx : (xt >= nx ? xt - nx : xt);
-  yt = yt < 0 ? yt + ny : (yt >= ny ? yt - ny : yt);
-  zt = zt < 0 ? zt + nz : (zt >= nz ? zt - nz : zt);
-  *dw = 0.f;
-  *dst = ((int64_t)zt * ny + yt) * nx + xt;
-  return i;
-}
-
 // Pull form of streaming on the tile-major lattice.  The stored state h
 // holds post-collision values; population q at node x before the next
 // collision is h_q(x - e_q), or, when x - e_q lies beyond the wall, the
