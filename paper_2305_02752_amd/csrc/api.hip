@@ -236,17 +236,9 @@ void interior_uniform(hc_ctx* c) {
   interior_update(c);
 }
 
-// One marking pass, or one per viscosity class in increasing order, so that
-// a site inside cells of several classes keeps the most viscous one.
 hipError_t mark_interior(hc_ctx* c, const Cells& C) {
-  if (c->n_vclass <= 1)
-    return launch_mark_interior(C, c->M, c->L, c->mask, nullptr, -1, c->B.flags, c->stream);
-  for (int k = 0; k < c->n_vclass; ++k) {
-    const hipError_t e =
-        launch_mark_interior(C, c->M, c->L, c->mask, c->cell_class, k, c->B.flags, c->stream);
-    if (e != hipSuccess) return e;
-  }
-  return hipSuccess;
+  return launch_mark_interior(C, c->M, c->L, c->mask, c->n_vclass <= 1 ? nullptr : c->cell_class, c->B.flags,
+                              c->stream);
 }
 
 void le_update(hc_ctx* c) {
@@ -1038,6 +1030,12 @@ hc_status hc_set_cell_viscosity(hc_ctx* c, const float* ratio, int64_t n_cells) 
   return HC_OK;
 }
 
+// Highest set bit of b (0 for 0).
+static uint8_t top_bit(uint8_t b) {
+  while (b & (b - 1)) b &= b - 1;
+  return b;
+}
+
 hc_status hc_read_interior(hc_ctx* c, uint8_t* host, int64_t n_sites) {
   HC_TRY(need_ws(c));
   if (!host || n_sites != c->L.n) return fail(c, HC_ERR_ARG, "site count mismatch");
@@ -1055,7 +1053,8 @@ hc_status hc_read_interior(hc_ctx* c, uint8_t* host, int64_t n_sites) {
   for (int z = 0; z < L.nz; ++z)
     for (int y = 0; y < L.ny; ++y)
       for (int x = 0; x < L.nx; ++x)
-        host[((int64_t)z * L.ny + y) * L.nx + x] = m[(size_t)site_of(L, x, y, z)];
+        // the most viscous of the classes marked there
+        host[((int64_t)z * L.ny + y) * L.nx + x] = top_bit(m[(size_t)site_of(L, x, y, z)]);
   return HC_OK;
 }
 

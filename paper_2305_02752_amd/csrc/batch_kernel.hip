@@ -151,7 +151,7 @@ __device__ inline void box_mark(const Batch& V, const BoxDesc& B, float* sp, con
   const long long nx = B.nx, ny = B.ny;
   inside::mark_cell(nullptr, sp, V.M.nv, V.M.tri, V.M.nt, o3, G,
                     [=](int x, int y, int z) { return ((int64_t)z * ny + y) * nx + x; },
-                    V.mask + B.site_off, (unsigned char)1, V.flags + 2, S, tid, nthr);
+                    [mask = V.mask + B.site_off](int64_t h) { mask[h] = 1; }, V.flags + 2, S, tid, nthr);
 }
 
 // Integer test: does the K-node stencil starting at node `base` meet rows [a, a + h)?

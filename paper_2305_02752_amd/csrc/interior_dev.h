@@ -55,17 +55,17 @@ __device__ inline bool edge_in(float px, float py, float qx, float qy, float x, 
   return w > 0.f || (w == 0.f && keep);
 }
 
-// Writes `bit` to mask[site(x, y, z)] for every lattice site inside the
+// Calls mark(site(x, y, z)) for every lattice site inside the
 // cell whose vertex offsets (from its integer origin o) are in sp [nv][3]
 // in LDS; with src non-null they are first copied there from src (global),
 // in the same pass that finds the cell's extent.  All nthr threads of the work-group call it (nthr a
 // multiple of 64, at most 1024); it synchronises the work-group.  A cell
 // too large for the column grid raises bit 4 of *err; more than kMaxCross
 // crossings on a column raise bit 5.
-template <class Site>
+template <class Site, class Mark>
 __device__ void mark_cell(const float* __restrict__ src, float* sp, int nv, const int* __restrict__ tri,
                           int nt, const int (&o)[3],
-                          const Grid& G, Site site, unsigned char* __restrict__ mask, unsigned char bit,
+                          const Grid& G, Site site, Mark mark,
                           int* err, Lds& S, int tid, int nthr) {
 #pragma clang fp contract(off)
   float lo[3] = {3e38f, 3e38f, 3e38f}, hi[3] = {-3e38f, -3e38f, -3e38f};
@@ -221,7 +221,7 @@ __device__ void mark_cell(const float* __restrict__ src, float* sp, int nv, cons
               zs = wrap(zs, G.n[2]);
             }
             const int64_t h = site(xs, ys, zs);
-            mask[h] = bit;
+            mark(h);
           }
         }
       }
