@@ -237,8 +237,8 @@ void interior_uniform(hc_ctx* c) {
 }
 
 hipError_t mark_interior(hc_ctx* c, const Cells& C) {
-  return launch_mark_interior(C, c->M, c->L, c->mask, c->n_vclass <= 1 ? nullptr : c->cell_class, c->B.flags,
-                              c->stream);
+  return launch_mark_interior(C, c->M, c->L, c->mask, c->n_vclass <= 1 ? nullptr : c->cell_class, c->n_vclass,
+                              c->B.flags, c->stream);
 }
 
 void le_update(hc_ctx* c) {

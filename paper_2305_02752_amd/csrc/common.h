@@ -200,12 +200,13 @@ hipError_t launch_tile_step(const Cells& c, const Mesh& m, const Lattice& L, con
                             const float* gin, float* gout, float* F, float4* macro, float4* partial,
                             bool fields, unsigned char* mask, hipStream_t s);
 // Mark the sites inside the cells in the site-ordered mask, which must hold
-// zeros on entry: bit k of a site's byte is set when it lies inside a cell of
-// viscosity class k (cls[c], or 0 for every cell when cls is null), whatever
-// the order of the cells.  The lattice pass takes the highest class and
-// clears the mask.
+// zeros on entry: the highest set bit of a site's byte is then the highest
+// viscosity class (cls[c] < n_class, or 0 for every cell when cls is null) of
+// the cells around it, whatever the order of the cells; lower classes may be
+// marked below it.  The lattice pass takes the highest class and clears the
+// mask.
 hipError_t launch_mark_interior(const Cells& c, const Mesh& m, const Lattice& L, unsigned char* mask,
-                                const unsigned char* cls, int* flags, hipStream_t s);
+                                const unsigned char* cls, int n_class, int* flags, hipStream_t s);
 // fused per-cell kernel: [advect of the pending step] + membrane + binning
 // (src: offsets to move from, or null to move in place; refresh: compute
 // the membrane forces, else hold the stored ones; ab2: Adams-Bashforth move)

@@ -139,6 +139,30 @@ def test_per_cell_classes_marks_and_overlap():
     assert np.array_equal(sim.read_interior(), (ref > 0).astype(np.uint8))
 
 
+@pytest.mark.parametrize("n_cells", [1279, 1280])
+def test_marks_of_two_classes_either_form(n_cells):
+    """The marks of two classes by atomics in one launch (up to 640 cells per
+    class) and by a launch per class: small overlapping cells, the higher
+    class on the shared sites, bit for bit the oracle's."""
+    from types import SimpleNamespace
+    from workloads.mesh import icosphere
+    v, tri = icosphere(2)
+    rest = 2.6 * v
+    rng = np.random.default_rng(52)
+    lat = Lattice(93, 88, 91, tau=0.9)
+    cells = place_cells(rest, rng.uniform(0, 88, (n_cells, 3)),
+                        np.stack([random_rotation(rng) for _ in range(n_cells)]), np.ones((n_cells, 4)) * 1e-3)
+    sim = make_sim(SimpleNamespace(lattice=lat, rest_pos=rest.astype(np.float32), tri=tri, cells=cells), cells)
+    sim.init_equilibrium()
+    ratios = np.where(rng.random(n_cells) < 0.5, 2.0, 5.0).astype(np.float32)
+    sim.set_cell_viscosity(ratios)
+    ref = _class_bits(cells.offsets, cells.origin, tri, lat, ratios)
+    print("bits", np.unique(ref, return_counts=True), flush=True)
+    assert (ref == 1).sum() > 5000 and (ref == 2).sum() > 5000
+    for _ in range(2):   # the second pass finds the marks cleared
+        assert np.array_equal(sim.read_interior(), ref)
+
+
 def test_coupled_parity_per_cell_ratios():
     w = tiny_periodic(seed=49, n=(32, 24, 20), n_cells=3, walls=2, body=(1e-5, 0, 0))
     rng = np.random.default_rng(50)
