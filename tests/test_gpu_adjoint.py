@@ -352,3 +352,50 @@ def test_adjoint_other_axes_and_ragged_sides(shape, wall):
     norm = np.linalg.norm(p * (g - g_cs)) / np.linalg.norm(p * g_cs)
     print(shape, wall, "p.g", p * g, "complex step", p * g_cs, "norm", norm, flush=True)
     assert norm <= 1e-4
+
+
+def test_adjoint_spread_in_several_chunks():
+    """Cells about one point, whose tiles hold more entries than the reverse
+    sweep's spread stages at once: derivatives of the summed loss along one
+    direction per parameter against the oracle's complex step."""
+    import dataclasses
+    from types import SimpleNamespace
+
+    from oracle import lattice as olat, step as ostep
+    from workloads.configs import random_rotation
+    rng = np.random.default_rng(71)
+    rest64, tri = rbc_mesh()
+    rest = rest64.astype(np.float32)
+    lat = Lattice(24, 24, 24, bc=(0, 0, 1), tau=0.95, wall_u_lo=(-0.01, 0, 0), wall_u_hi=(0.01, 0, 0))
+    nc, n = 4, 24
+    cells = place_cells(rest64, 11.5 + rng.uniform(-0.4, 0.4, (nc, 3)),
+                        np.stack([random_rotation(rng) for _ in range(nc)]),
+                        K_REF * 10.0 ** rng.uniform(-0.3, 0.3, (nc, 4)),
+                        traction=np.stack([rng.uniform(-3e-3, 3e-3, nc), np.zeros(nc), np.zeros(nc)], 1))
+    targets = 16.0 * rng.uniform(0.8, 1.2, (nc, 2))
+    sim = make_sim(SimpleNamespace(lattice=lat, rest_pos=rest, tri=tri, cells=cells), cells)
+    sim.init_equilibrium()
+    longest = int(np.diff(sim.read_bins()[1]).max())
+    sim.adj_bind(n, 8)
+    loss = sim.adj_forward(targets.reshape(-1))
+    g = sim.adj_backward()
+    kk = cells.k.astype(np.float64)
+    w = kk * rng.uniform(0.5, 1.5, (nc, 4))
+    got = np.concatenate([(w * g[:, :4]).sum(0), [lat.tau * g[0, 4]]])
+    ref, h = np.zeros(5), 1e-30
+    for j in range(5):
+        k = kk.astype(np.complex128)
+        tau = lat.tau + 0j
+        if j < 4:
+            k[:, j] += 1j * h * w[:, j]
+        else:
+            tau += 1j * h * lat.tau
+        m = ostep.make_model(dataclasses.replace(lat, tau=tau), rest.astype(np.float64), tri, k, cells.traction.astype(np.float64))
+        _, X = ostep.run(m, olat.init_equilibrium(lat.shape), cells.positions64(), n)
+        L = sum(oadj.loss_of(X[c], targets[c]) for c in range(nc))
+        ref[j] = L.imag / h
+    norm = np.linalg.norm(got - ref) / np.linalg.norm(ref)
+    print("longest list", longest, "loss", loss.sum(), L.real, "got", got, "ref", ref, "norm", norm, flush=True)
+    assert longest > 512
+    assert abs(loss.sum() - L.real) <= 1e-5 * L.real
+    assert norm <= 1e-4
