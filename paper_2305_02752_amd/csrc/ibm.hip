@@ -317,6 +317,7 @@ struct Smem {
   int cnt[kKeys];           // records per box shape, then the first record of each shape
   unsigned fmax;            // largest force component magnitude (float bits)
   int fsum;                 // sum of the entries' largest components, in units of fmax 2^-bexp
+  int bad;                  // some node's velocity is not finite
   int image[I64 ? kStage : 1];   // image index of the record's nodes
   // The velocity takes the accumulator's place, each node's in the slots of
   // its own sums, so the thread that owns a node needs no other's data.
@@ -683,6 +684,10 @@ __device__ __forceinline__ void spread(int m, const Lattice& L, int ne, int kexp
 // held in S.acc (float bits), summed over the in-tile nodes in stencil
 // order, into the records' partial-sum slots.
 // With sheared images every node carries its image's velocity.
+// x slots past the entry's count, whose weight is zero, read on along the
+// row, so that a row's reads share one address.  With SMALL, and so in a tile
+// with a velocity that is not finite, they read the entry's first node again:
+// a node outside the stencil may not reach the vertex, and 0 x NaN would.
 template <int K, bool SMALL, bool LE>
 __device__ __forceinline__ void interp(int m, const Lattice& L, const Smem<LE>& S, int64_t stride,
                                        float4* __restrict__ partial) {
@@ -693,8 +698,8 @@ __device__ __forceinline__ void interp(int m, const Lattice& L, const Smem<LE>& 
     decode<K, SMALL>(run, pos.x, L.nx, X);
     decode<K, SMALL>(run >> 8, pos.y, L.ny, Y);
     decode<K, SMALL>(run >> 16, pos.z, L.nz, Z);
-    // x slots past the entry's count carry weight zero and read on along the
-    // row, so a row's reads have no branch and issue together
+    // x slots past the entry's count carry weight zero, so a row's reads have
+    // no branch and issue together
     float wx[K];
 #pragma unroll
     for (int s = 0; s < K; ++s) wx[s] = s < X.n ? X.w[s] : 0.f;
@@ -711,7 +716,7 @@ __device__ __forceinline__ void interp(int m, const Lattice& L, const Smem<LE>& 
         float rx = 0.f, ry = 0.f, rz = 0.f;
 #pragma unroll
         for (int ix = 0; ix < K; ++ix) {
-          const float3 u = S.get_u(row + node<SMALL>(X.l0, ix, L.nx));
+          const float3 u = S.get_u(row + node<SMALL>(X.l0, SMALL && ix >= X.n ? 0 : ix, L.nx));
           rx += wx[ix] * (LE ? u.x + shift : u.x);
           ry += wx[ix] * u.y;
           rz += wx[ix] * u.z;
@@ -835,6 +840,7 @@ __device__ __forceinline__ void tile_step_sorted_body(CT C, MT M, LT L, BT B,
   if (threadIdx.x == 0) {
     S.fmax = 0u;
     S.fsum = 0;
+    S.bad = 0;
   }
   const int ne = C.n > 0 ? min(B.touch_cnt[t], B.cap) : 0;
   __syncthreads();
@@ -921,6 +927,7 @@ __device__ __forceinline__ void tile_step_sorted_body(CT C, MT M, LT L, BT B,
     }
     lbm::collide(g, fx, fy, fz, omega, rho, ux, uy, uz);
     S.put_u(li, ux, uy, uz);
+    if (!(fabsf(ux) + fabsf(uy) + fabsf(uz) < 3e38f)) S.bad = 1;
     if (fields) {
       macro[h] = make_float4(ux, uy, uz, rho);
       F[h] = fx;
@@ -943,8 +950,9 @@ __device__ __forceinline__ void tile_step_sorted_body(CT C, MT M, LT L, BT B,
   if (ne == 0) return;
   lds_barrier();   // the velocities; the populations' stores need no wait
   const int64_t stride = (int64_t)C.n * M.nv;
+  const bool clip = small || __builtin_amdgcn_readfirstlane(S.bad);
   auto interp = [&](int m) {
-    if (small) srt::interp<K, true>(m, L, S, stride, partial);
+    if (clip) srt::interp<K, true>(m, L, S, stride, partial);
     else srt::interp<K, false>(m, L, S, stride, partial);
   };
   if (ne <= srt::kStage) {

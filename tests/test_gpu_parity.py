@@ -554,3 +554,50 @@ def test_binning_bit_exact_at_the_table_edges(case):
     assert np.array_equal(owner, ow)
     assert np.array_equal(cptr, cptr_r) and np.array_equal(clist, clist_r)
     assert np.array_equal(tptr, tptr_r) and np.array_equal(touch, touch_r)
+
+
+@pytest.mark.parametrize("n,kernel,le_u", [
+    ((24, 20, 16), 4, 0.0),
+    ((24, 20, 16), 2, 0.0),
+    ((24, 9, 20), 4, 0.0),       # an axis short enough for the wrapping form
+    ((24, 17, 16), 4, 0.02),     # sheared images
+])
+def test_nodes_beyond_a_stencil_do_not_reach_its_vertex(n, kernel, le_u):
+    """A node that no stencil contains, next to nodes that some do, holds NaN:
+    the step succeeds and every vertex moves as without it, bit for bit."""
+    from types import SimpleNamespace
+    from workloads import rbc_mesh
+    rest64, tri = rbc_mesh()
+    rng = np.random.default_rng(93)
+    lat = Lattice(*n, tau=0.9, ibm_kernel=kernel, lees_edwards_u=le_u)
+    cells = jitter_cells(rng, place_cells(0.45 * rest64, np.array(n)[None] * 0.5, np.eye(3)[None], K_REF[None],
+                                          traction=[[2e-3, 0, 0]]), 0.03)
+    w = SimpleNamespace(lattice=lat, rest_pos=(0.45 * rest64).astype(np.float32), tri=tri, cells=cells)
+    # the nodes of every stencil, and up to 3 more along x from its last node inside a tile
+    used, near = (np.zeros(n, dtype=bool) for _ in range(2))
+    b = cells.origin[0] + np.floor(cells.offsets[0]).astype(int) - (1 if kernel == 4 else 0)
+    for v in b:
+        ix = [(v[d] + np.arange(kernel)) % n[d] for d in range(3)]
+        used[np.ix_(*ix)] = True
+        for t in set(ix[0] // 8):
+            run = ix[0][ix[0] // 8 == t]
+            past = run[0] + np.arange(len(run), kernel)
+            near[np.ix_(past[(past < 8 * t + 8) & (past < n[0])], ix[1], ix[2])] = True
+    at = np.argwhere(near & ~used)
+    print(n, kernel, le_u, "nodes next to stencils", len(at), flush=True)
+    assert len(at) > 0
+    g0 = random_shifted_populations(rng, lat, 1e-3)
+    res = []
+    for bad in (False, True):
+        g = g0.copy()
+        if bad:
+            g[:, at[:, 2], at[:, 1], at[:, 0]] = np.nan
+        sim = make_sim(w, cells)
+        sim.write_populations(g)
+        sim.step(1)
+        sim.sync()
+        o, off, _ = sim.read_vertices()
+        res.append((sim.read_vertex_velocity(), o, off))
+        assert np.isnan(sim.read_populations()).any() == bad
+    for a, c in zip(*res):
+        assert np.array_equal(a, c)
