@@ -176,25 +176,18 @@ hipError_t launch_cell_step(const Cells& c, const Mesh& m, const Lattice& L, con
   return hipGetLastError();
 }
 
-// Boxes of one shape without sheared images; every box holds the same number
-// of cells.
+// Boxes of one shape with the 4-point kernel (the reverse sweep's), without
+// sheared images; every box holds the same number of cells.
 hipError_t launch_cell_step_multi(const CellStepArgs& a0, const CellStepArgs* dev, int n, hipStream_t s) {
   if (n == 0 || a0.C.n == 0) return hipSuccess;
-  if (a0.L.le) return hipErrorInvalidValue;
+  if (a0.L.le || a0.L.kernel != 4) return hipErrorInvalidValue;
   const int region = std::max(24, bin::slot_lds_per_vertex(a0.L.max_touch)) * a0.M.nv;
   const size_t lds = (size_t)((region + 7) & ~7) + (size_t)a0.M.nv * 3 * sizeof(float);
   const dim3 grid((unsigned)a0.C.n, (unsigned)n);
   auto go = [&](auto kern, int threads) { hipLaunchKernelGGL(kern, grid, dim3(threads), lds, s, dev); };
-  if (a0.C.n <= 64) {
-    if (a0.L.kernel == 4) go(k_cell_step_multi<4, 1024>, 1024);
-    else go(k_cell_step_multi<2, 1024>, 1024);
-  } else if (a0.C.n <= 1024) {
-    if (a0.L.kernel == 4) go(k_cell_step_multi<4, 512>, 512);
-    else go(k_cell_step_multi<2, 512>, 512);
-  } else {
-    if (a0.L.kernel == 4) go(k_cell_step_multi<4, 256>, 256);
-    else go(k_cell_step_multi<2, 256>, 256);
-  }
+  if (a0.C.n <= 64) go(k_cell_step_multi<4, 1024>, 1024);
+  else if (a0.C.n <= 1024) go(k_cell_step_multi<4, 512>, 512);
+  else go(k_cell_step_multi<4, 256>, 256);
   return hipGetLastError();
 }
 

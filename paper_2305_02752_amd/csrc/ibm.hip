@@ -786,12 +786,11 @@ __global__ __launch_bounds__(256) void k_spread_multi(const SpreadArgs* __restri
   spread_body<K, const Cells&, const Mesh&, const Lattice&, const Bins&>(a.C, a.M, a.L, a.B, a.vec, a.body, a.F);
 }
 
-constexpr int kNoWall = -1, kAnyWall = 3;
+constexpr int kNoWall = -1;
 
 // The fused lattice pass, one work-group per tile, with the sorted-entry IBM
-// phases (WA: the wall axis, kNoWall, or kAnyWall when boxes of one launch may
-// differ in it; LE: with sheared images and two or more tiles along
-// z, which leave an entry's nodes in one image):
+// phases (WA: the wall axis or kNoWall; LE: with sheared images and two or more
+// tiles along z, which leave an entry's nodes in one image):
 //  1. stage the tile's entries (records ordered by in-tile box shape) and
 //     spread their forces into LDS (int32 fixed point at the tile's scale);
 //  2. pull-stream + collide the tile's nodes (force = body force + spread
@@ -816,8 +815,9 @@ constexpr int kNoWall = -1, kAnyWall = 3;
 // six waves per SIMD then 238 us for 255 on 64 boxes of 48^3): a reference to
 // a kernel's by-value parameter, or a by-value copy of a record in global
 // memory, would put the lattice record in scratch.  The wall axis is a
-// compile-time choice of the single-box kernel: 52.5 us for 54.5 on a walled
-// 128 x 64 x 64, 19.6 for 21.4 on 32^3.
+// compile-time choice of both (the boxes of a launch share it): 52.5 us for
+// 54.5 on a walled 128 x 64 x 64, 19.6 for 21.4 on 32^3, 234 for 238 on the 64
+// boxes.
 template <int K, int WA, bool LE, class CT, class MT, class LT, class BT>
 __device__ __forceinline__ void tile_step_sorted_body(CT C, MT M, LT L, BT B,
                                                       const float* __restrict__ gin,
@@ -827,7 +827,7 @@ __device__ __forceinline__ void tile_step_sorted_body(CT C, MT M, LT L, BT B,
                                                       unsigned char* __restrict__ mask) {
   __shared__ srt::Smem<LE> S;
   constexpr bool W = WA != kNoWall;
-  const int wa = WA == kAnyWall ? L.wall_axis : WA;
+  constexpr int wa = WA;
   const int t = tile_of_block(L, blockIdx.x);
   if (t < 0) return;
   int x0, y0, z0;
@@ -1092,39 +1092,33 @@ __global__ __launch_bounds__(256) void k_advect(Cells C, Mesh M, Lattice L, Bins
 
 }  // namespace
 
+// The reverse sweep differentiates the 4-point function; the spread and the
+// batched launches are part of it and have no 2-point form.
 hipError_t launch_spread_vec(const Cells& c, const Mesh& m, const Lattice& L, const Bins& b,
                              const float* vec, float body, float* F, hipStream_t s) {
-  if (L.kernel == 4)
-    hipLaunchKernelGGL(k_spread<4>, dim3(L.ntiles), dim3(256), 0, s, c, m, L, b, vec, body, F);
-  else
-    hipLaunchKernelGGL(k_spread<2>, dim3(L.ntiles), dim3(256), 0, s, c, m, L, b, vec, body, F);
+  if (L.kernel != 4) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_spread<4>, dim3(L.ntiles), dim3(256), 0, s, c, m, L, b, vec, body, F);
   return hipGetLastError();
 }
 
 hipError_t launch_spread_vec_multi(const SpreadArgs& a0, const SpreadArgs* dev, int n, hipStream_t s) {
   if (n == 0) return hipSuccess;
-  const dim3 grid((unsigned)a0.L.ntiles, (unsigned)n);
-  if (a0.L.kernel == 4)
-    hipLaunchKernelGGL(k_spread_multi<4>, grid, dim3(256), 0, s, dev);
-  else
-    hipLaunchKernelGGL(k_spread_multi<2>, grid, dim3(256), 0, s, dev);
+  if (a0.L.kernel != 4) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_spread_multi<4>, dim3((unsigned)a0.L.ntiles, (unsigned)n), dim3(256), 0, s, dev);
   return hipGetLastError();
 }
 
-// Boxes of one shape and one kind of boundary (walled or not), without
-// sheared images.
+// Boxes of one shape and one set of boundaries, without sheared images.
 hipError_t launch_tile_step_multi(const TileStepArgs& a0, const TileStepArgs* dev, int n, hipStream_t s) {
   if (n == 0) return hipSuccess;
-  if (a0.L.le) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)tile_grid(a0.L), (unsigned)n);
-  const bool w = a0.L.wall_axis >= 0;
-  if (a0.L.kernel == 4) {
-    if (w) hipLaunchKernelGGL((k_tile_step_sorted_multi<4, kAnyWall>), grid, dim3(256), 0, s, dev);
-    else hipLaunchKernelGGL((k_tile_step_sorted_multi<4, kNoWall>), grid, dim3(256), 0, s, dev);
-  } else {
-    if (w) hipLaunchKernelGGL((k_tile_step_sorted_multi<2, kAnyWall>), grid, dim3(256), 0, s, dev);
-    else hipLaunchKernelGGL((k_tile_step_sorted_multi<2, kNoWall>), grid, dim3(256), 0, s, dev);
-  }
+  if (a0.L.le || a0.L.kernel != 4) return hipErrorInvalidValue;
+  auto go = [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3((unsigned)tile_grid(a0.L), (unsigned)n), dim3(256), 0, s, dev);
+  };
+  if (a0.L.wall_axis == 0) go(k_tile_step_sorted_multi<4, 0>);
+  else if (a0.L.wall_axis == 1) go(k_tile_step_sorted_multi<4, 1>);
+  else if (a0.L.wall_axis == 2) go(k_tile_step_sorted_multi<4, 2>);
+  else go(k_tile_step_sorted_multi<4, kNoWall>);
   return hipGetLastError();
 }
 

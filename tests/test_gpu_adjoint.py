@@ -325,6 +325,45 @@ def test_multi_box_adjoint_equals_single_box():
         s.close()
 
 
+@pytest.mark.parametrize("wall", [0, 1, 2, -1])
+def test_multi_box_adjoint_on_every_wall_axis(wall):
+    """Two boxes of ragged sides, walls on each axis in turn: the batched
+    kernels' loss and gradient against the single-box ones, with the bars of
+    the cubes above."""
+    from types import SimpleNamespace
+
+    from paper_2305_02752_amd import Simulation
+    rng = np.random.default_rng(33)
+    rest64, tri = rbc_mesh()
+    bc, u = [0, 0, 0], [0.0, 0.0, 0.0]
+    if wall >= 0:
+        bc[wall] = 1
+        u[(wall + 1) % 3] = 0.01
+    n, ck, shape = 20, 8, (20, 19, 21)
+    targets = np.array([16.0 * 1.2, 16.0 * 0.9])
+    sims, single = [], []
+    for tau in (0.9, 1.05):
+        lat = Lattice(*shape, bc=tuple(bc), tau=tau, wall_u_lo=tuple(-x for x in u), wall_u_hi=tuple(u))
+        centre = (np.array(shape) - 1) / 2.0 + rng.uniform(-0.5, 0.5, 3)
+        cells = place_cells(rest64, centre[None], small_rotation(rng, 5.0)[None], K_REF[None],
+                            traction=[[3e-3, 0.0, 0.0]])
+        rest = rest64.astype(np.float32)
+        loss, g, sim = _device_grad(lat, rest, tri, cells, targets, n, ck)
+        single.append((loss, g))
+        sim.close()
+        sims.append(make_sim(SimpleNamespace(lattice=lat, rest_pos=rest, tri=tri, cells=cells), cells))
+        sims[-1].init_equilibrium()
+        sims[-1].adj_bind(n, ck)
+    loss = Simulation.adj_multi_forward(sims, np.repeat(targets[None, None], 2, 0))
+    g = Simulation.adj_multi_backward(sims)
+    for b in range(2):
+        err = np.linalg.norm(g[b, 0] - single[b][1]) / np.linalg.norm(single[b][1])
+        print(wall, "loss", loss[b], single[b][0], "gradient", g[b, 0], "norm", err, flush=True)
+        assert np.allclose(loss[b], single[b][0], rtol=1e-7, atol=0)
+        assert err <= 1e-6
+        sims[b].close()
+
+
 @pytest.mark.parametrize("shape,wall", [((20, 18, 21), 0), ((17, 24, 10), 1), ((9, 20, 24), -1)])
 def test_adjoint_other_axes_and_ragged_sides(shape, wall):
     """Walls on the other axes, sides that leave partial tiles and a periodic
