@@ -15,6 +15,7 @@
 // Integer addition is associative, so the result is bitwise independent of
 // the order in which waves and lanes arrive -- no global atomics, no
 // run-to-run drift.
+#include <algorithm>
 #include <type_traits>
 
 #include "ibm_dev.h"
@@ -317,7 +318,7 @@ struct Smem {
   int cnt[kKeys];           // records per box shape, then the first record of each shape
   unsigned fmax;            // largest force component magnitude (float bits)
   int fsum;                 // sum of the entries' largest components, in units of fmax 2^-bexp
-  int bad;                  // some node's velocity is not finite
+  int bad;                  // some node's velocity is not finite (4-point kernel)
   int image[I64 ? kStage : 1];   // image index of the record's nodes
   // The velocity takes the accumulator's place, each node's in the slots of
   // its own sums, so the thread that owns a node needs no other's data.
@@ -340,6 +341,14 @@ struct Smem {
                        reinterpret_cast<const float*>(acc[2])[i]);
   }
 };
+
+// (16 bytes a store: 2.24 -> 2.23 ms on 256 x 256 x 512 sites, 18,600 cells)
+template <bool I64>
+__device__ __forceinline__ void clear_sums(Smem<I64>& S) {
+  static_assert(sizeof(S.acc) % sizeof(int4) == 0, "sums in whole 16-byte words");
+  for (int i = threadIdx.x; i < (int)(sizeof(S.acc) / sizeof(int4)); i += kThreads)
+    reinterpret_cast<int4*>(S.acc)[i] = make_int4(0, 0, 0, 0);
+}
 
 // In-tile run along one axis: the K positions base + k (wrapped on a periodic
 // axis, dropped past a wall) meet the tile's nodes [t0, t0 + 8) in one run of
@@ -684,11 +693,13 @@ __device__ __forceinline__ void spread(int m, const Lattice& L, int ne, int kexp
 // held in S.acc (float bits), summed over the in-tile nodes in stencil
 // order, into the records' partial-sum slots.
 // With sheared images every node carries its image's velocity.
-// x slots past the entry's count, whose weight is zero, read on along the
-// row, so that a row's reads share one address.  With SMALL, and so in a tile
-// with a velocity that is not finite, they read the entry's first node again:
-// a node outside the stencil may not reach the vertex, and 0 x NaN would.
-template <int K, bool SMALL, bool LE>
+// CLIP: x slots past the entry's count, whose weight is zero, read its first
+// node again: a node outside the stencil may not reach the vertex, and 0 x NaN
+// would.  Without it they read on along the row, so that a row's reads share
+// one address; that is for tiles whose velocities are all finite.  With two
+// nodes a row the select costs less than the test for them (a pass of 240 tiles
+// 13.94 us for 14.20).
+template <int K, bool SMALL, bool CLIP, bool LE>
 __device__ __forceinline__ void interp(int m, const Lattice& L, const Smem<LE>& S, int64_t stride,
                                        float4* __restrict__ partial) {
   for (int i = threadIdx.x; i < m; i += blockDim.x) {
@@ -716,7 +727,7 @@ __device__ __forceinline__ void interp(int m, const Lattice& L, const Smem<LE>& 
         float rx = 0.f, ry = 0.f, rz = 0.f;
 #pragma unroll
         for (int ix = 0; ix < K; ++ix) {
-          const float3 u = S.get_u(row + node<SMALL>(X.l0, SMALL && ix >= X.n ? 0 : ix, L.nx));
+          const float3 u = S.get_u(row + node<SMALL>(X.l0, CLIP && ix >= X.n ? 0 : ix, L.nx));
           rx += wx[ix] * (LE ? u.x + shift : u.x);
           ry += wx[ix] * u.y;
           rz += wx[ix] * u.z;
@@ -746,11 +757,7 @@ __device__ __forceinline__ void spread_body(CT C, MT M, LT L, BT B, const float*
   const int t = blockIdx.x;
   int x0, y0, z0;
   tile_origin(L, t, x0, y0, z0);
-  for (int i = threadIdx.x; i < srt::kNodes; i += blockDim.x) {
-    S.acc[0][i] = 0;
-    S.acc[1][i] = 0;
-    S.acc[2][i] = 0;
-  }
+  srt::clear_sums(S);
   const int ne = min(B.touch_cnt[t], B.cap);
   lds_barrier();
   const bool small = min(L.nx, min(L.ny, L.nz)) <= srt::kSmall;
@@ -789,8 +796,9 @@ __global__ __launch_bounds__(256) void k_spread_multi(const SpreadArgs* __restri
 constexpr int kNoWall = -1;
 
 // The fused lattice pass, one work-group per tile, with the sorted-entry IBM
-// phases (WA: the wall axis or kNoWall; LE: with sheared images and two or more
-// tiles along z, which leave an entry's nodes in one image):
+// phases (WA: the wall axis or kNoWall; SMALL: some axis has up to srt::kSmall
+// nodes; LE: with sheared images and two or more tiles along z, which leave an
+// entry's nodes in one image):
 //  1. stage the tile's entries (records ordered by in-tile box shape) and
 //     spread their forces into LDS (int32 fixed point at the tile's scale);
 //  2. pull-stream + collide the tile's nodes (force = body force + spread
@@ -818,7 +826,7 @@ constexpr int kNoWall = -1;
 // compile-time choice of both (the boxes of a launch share it): 52.5 us for
 // 54.5 on a walled 128 x 64 x 64, 19.6 for 21.4 on 32^3, 234 for 238 on the 64
 // boxes.
-template <int K, int WA, bool LE, class CT, class MT, class LT, class BT>
+template <int K, int WA, bool SMALL, bool LE, class CT, class MT, class LT, class BT>
 __device__ __forceinline__ void tile_step_sorted_body(CT C, MT M, LT L, BT B,
                                                       const float* __restrict__ gin,
                                                       float* __restrict__ gout, float* __restrict__ F,
@@ -832,11 +840,7 @@ __device__ __forceinline__ void tile_step_sorted_body(CT C, MT M, LT L, BT B,
   if (t < 0) return;
   int x0, y0, z0;
   tile_origin(L, t, x0, y0, z0);
-  for (int i = threadIdx.x; i < srt::kNodes; i += blockDim.x) {
-    S.acc[0][i] = 0;
-    S.acc[1][i] = 0;
-    S.acc[2][i] = 0;
-  }
+  srt::clear_sums(S);
   if (threadIdx.x == 0) {
     S.fmax = 0u;
     S.fsum = 0;
@@ -847,7 +851,6 @@ __device__ __forceinline__ void tile_step_sorted_body(CT C, MT M, LT L, BT B,
   // every thread has read the count: leave it zero for the next binning
   if (ne > 0 && threadIdx.x == 0) B.touch_cnt[t] = 0;
   int kexp = 0;
-  const bool small = min(L.nx, min(L.ny, L.nz)) <= srt::kSmall;
   if (ne > 0) {
     // the scale must cover every chunk (the int64 sums need none)
     const bool bound = !LE && ne <= srt::kStage;
@@ -857,8 +860,7 @@ __device__ __forceinline__ void tile_step_sorted_body(CT C, MT M, LT L, BT B,
       srt::stage<K, LE>(C, M, L, B, C.force, t, x0, y0, z0, e0, m, true, bound, S);
       if (!LE && e0 == 0)
         kexp = srt::fix_exponent(S.fsum, __uint_as_float(S.fmax), srt::max_node_weight(L), B.bexp);
-      if (small) srt::spread<K, true>(m, L, ne, kexp, S);
-      else srt::spread<K, false>(m, L, ne, kexp, S);
+      srt::spread<K, SMALL>(m, L, ne, kexp, S);
       __syncthreads();
     }
   }
@@ -927,7 +929,7 @@ __device__ __forceinline__ void tile_step_sorted_body(CT C, MT M, LT L, BT B,
     }
     lbm::collide(g, fx, fy, fz, omega, rho, ux, uy, uz);
     S.put_u(li, ux, uy, uz);
-    if (!(fabsf(ux) + fabsf(uy) + fabsf(uz) < 3e38f)) S.bad = 1;
+    if (K == 4 && !(fabsf(ux) + fabsf(uy) + fabsf(uz) < 3e38f)) S.bad = 1;
     if (fields) {
       macro[h] = make_float4(ux, uy, uz, rho);
       F[h] = fx;
@@ -950,10 +952,10 @@ __device__ __forceinline__ void tile_step_sorted_body(CT C, MT M, LT L, BT B,
   if (ne == 0) return;
   lds_barrier();   // the velocities; the populations' stores need no wait
   const int64_t stride = (int64_t)C.n * M.nv;
-  const bool clip = small || __builtin_amdgcn_readfirstlane(S.bad);
+  const bool clip = K == 2 || __builtin_amdgcn_readfirstlane(S.bad);
   auto interp = [&](int m) {
-    if (clip) srt::interp<K, true>(m, L, S, stride, partial);
-    else srt::interp<K, false>(m, L, S, stride, partial);
+    if (clip) srt::interp<K, SMALL, true>(m, L, S, stride, partial);
+    else srt::interp<K, SMALL, false>(m, L, S, stride, partial);
   };
   if (ne <= srt::kStage) {
     interp(ne);
@@ -969,7 +971,7 @@ __device__ __forceinline__ void tile_step_sorted_body(CT C, MT M, LT L, BT B,
   }
 }
 
-template <int K, int WA>
+template <int K, int WA, bool SMALL>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void k_tile_step_sorted(
     Cells C, Mesh M, Lattice L, Bins B,
                                                           const float* __restrict__ gin,
@@ -978,29 +980,29 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void k
                                                           float4* __restrict__ macro,
                                                           float4* __restrict__ partial, int fields,
                                                           unsigned char* __restrict__ mask) {
-  tile_step_sorted_body<K, WA, false, Cells, Mesh, Lattice, Bins>(C, M, L, B, gin, gout, F, macro, partial, fields,
+  tile_step_sorted_body<K, WA, SMALL, false, Cells, Mesh, Lattice, Bins>(C, M, L, B, gin, gout, F, macro, partial, fields,
                                                                  mask);
 }
 
 // Sheared images.  The entry-parallel form below tests every axis slot at
 // every node and keeps its entries unsorted: 379 us on 128^3 with 1160 cells,
 // this one 224 us.  Bound by the 64-bit LDS atomics of the spread.
-template <int K>
+template <int K, bool SMALL>
 __global__ __launch_bounds__(256) void k_tile_step_sorted_le(Cells C, Mesh M, Lattice L, Bins B,
                                                              const float* __restrict__ gin,
                                                              float* __restrict__ gout, float* __restrict__ F,
                                                              float4* __restrict__ macro,
                                                              float4* __restrict__ partial, int fields,
                                                              unsigned char* __restrict__ mask) {
-  tile_step_sorted_body<K, kNoWall, true, Cells, Mesh, Lattice, Bins>(C, M, L, B, gin, gout, F, macro, partial, fields,
+  tile_step_sorted_body<K, kNoWall, SMALL, true, Cells, Mesh, Lattice, Bins>(C, M, L, B, gin, gout, F, macro, partial, fields,
                                                                     mask);
 }
 
 // Batched form: box blockIdx.y.
-template <int K, int WA>
+template <int K, int WA, bool SMALL>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void k_tile_step_sorted_multi(const TileStepArgs* __restrict__ many) {
   const TileStepArgs& a = launch_record(many, blockIdx.y);
-  tile_step_sorted_body<K, WA, false, const Cells&, const Mesh&, const Lattice&, const Bins&>(
+  tile_step_sorted_body<K, WA, SMALL, false, const Cells&, const Mesh&, const Lattice&, const Bins&>(
       a.C, a.M, a.L, a.B, a.gin, a.gout, a.F, a.macro, a.partial, a.fields, a.mask);
 }
 
@@ -1092,6 +1094,15 @@ __global__ __launch_bounds__(256) void k_advect(Cells C, Mesh M, Lattice L, Bins
 
 }  // namespace
 
+// f(whether the lattice needs the wrapping form, as a compile-time constant).
+// One form per kernel: with both in one, a pass over 240 tiles of few entries
+// (2-point kernel, 91 x 25 x 40, 27 cells) took 14.0 us for 13.9.
+template <class F>
+static void with_small(const Lattice& L, F f) {
+  if (std::min(L.nx, std::min(L.ny, L.nz)) <= srt::kSmall) f(std::true_type());
+  else f(std::false_type());
+}
+
 // The reverse sweep differentiates the 4-point function; the spread and the
 // batched launches are part of it and have no 2-point form.
 hipError_t launch_spread_vec(const Cells& c, const Mesh& m, const Lattice& L, const Bins& b,
@@ -1115,10 +1126,13 @@ hipError_t launch_tile_step_multi(const TileStepArgs& a0, const TileStepArgs* de
   auto go = [&](auto kern) {
     hipLaunchKernelGGL(kern, dim3((unsigned)tile_grid(a0.L), (unsigned)n), dim3(256), 0, s, dev);
   };
-  if (a0.L.wall_axis == 0) go(k_tile_step_sorted_multi<4, 0>);
-  else if (a0.L.wall_axis == 1) go(k_tile_step_sorted_multi<4, 1>);
-  else if (a0.L.wall_axis == 2) go(k_tile_step_sorted_multi<4, 2>);
-  else go(k_tile_step_sorted_multi<4, kNoWall>);
+  with_small(a0.L, [&](auto small) {
+    constexpr bool S = decltype(small)::value;
+    if (a0.L.wall_axis == 0) go(k_tile_step_sorted_multi<4, 0, S>);
+    else if (a0.L.wall_axis == 1) go(k_tile_step_sorted_multi<4, 1, S>);
+    else if (a0.L.wall_axis == 2) go(k_tile_step_sorted_multi<4, 2, S>);
+    else go(k_tile_step_sorted_multi<4, kNoWall, S>);
+  });
   return hipGetLastError();
 }
 
@@ -1129,17 +1143,20 @@ hipError_t launch_tile_step(const Cells& c, const Mesh& m, const Lattice& L, con
     hipLaunchKernelGGL(kern, dim3((unsigned)tile_grid(L)), dim3(256), 0, s, c, m, L, b, gin, gout, F, macro, partial,
                        fields ? 1 : 0, mask);
   };
-  auto form = [&](auto k) {
+  auto form = [&](auto k, auto small) {
     constexpr int K = decltype(k)::value;
+    constexpr bool S = decltype(small)::value;
     if (L.le && L.tz == 1) go(k_tile_step_le_thin<K>);   // an entry's nodes may lie in two images
-    else if (L.le) go(k_tile_step_sorted_le<K>);
-    else if (L.wall_axis == 0) go(k_tile_step_sorted<K, 0>);
-    else if (L.wall_axis == 1) go(k_tile_step_sorted<K, 1>);
-    else if (L.wall_axis == 2) go(k_tile_step_sorted<K, 2>);
-    else go(k_tile_step_sorted<K, kNoWall>);
+    else if (L.le) go(k_tile_step_sorted_le<K, S>);
+    else if (L.wall_axis == 0) go(k_tile_step_sorted<K, 0, S>);
+    else if (L.wall_axis == 1) go(k_tile_step_sorted<K, 1, S>);
+    else if (L.wall_axis == 2) go(k_tile_step_sorted<K, 2, S>);
+    else go(k_tile_step_sorted<K, kNoWall, S>);
   };
-  if (L.kernel == 4) form(std::integral_constant<int, 4>());
-  else form(std::integral_constant<int, 2>());
+  with_small(L, [&](auto small) {
+    if (L.kernel == 4) form(std::integral_constant<int, 4>(), small);
+    else form(std::integral_constant<int, 2>(), small);
+  });
   return hipGetLastError();
 }
 
