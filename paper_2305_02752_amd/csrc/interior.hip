@@ -24,6 +24,9 @@ constexpr int kMarkThreads = 256;
 // 253 and 210 at 9300.
 constexpr int kCellsPerClass = 640;
 
+// JOIN: atomically, whatever the cell's class; else plain stores for the cells
+// of one class (only_class, or all of them when negative).
+template <bool JOIN>
 __global__ __launch_bounds__(kMarkThreads) void k_mark_interior(Cells C, Mesh M, Lattice L,
                                                                 unsigned char* __restrict__ mask,
                                                                 const unsigned char* __restrict__ cls,
@@ -31,7 +34,7 @@ __global__ __launch_bounds__(kMarkThreads) void k_mark_interior(Cells C, Mesh M,
   extern __shared__ float sp[];   // [nv][3] offsets
   __shared__ inside::Lds S;
   const int c = blockIdx.x, tid = threadIdx.x;
-  if (only_class >= 0 && cls[c] != only_class) return;   // another class's launch
+  if (!JOIN && only_class >= 0 && cls[c] != only_class) return;   // another class's launch
   const int64_t b3 = (int64_t)c * M.nv * 3;
   const int o[3] = {C.origin[3 * c], C.origin[3 * c + 1], C.origin[3 * c + 2]};
   inside::Grid G;
@@ -43,7 +46,7 @@ __global__ __launch_bounds__(kMarkThreads) void k_mark_interior(Cells C, Mesh M,
   G.le_delta = L.le_delta;
   const unsigned bit = 1u << (cls ? cls[c] : 0);
   auto mark = [&](int64_t h) {
-    if (cls && only_class < 0) atomicOr(reinterpret_cast<unsigned*>(mask) + (h >> 2), bit << (8 * (int)(h & 3)));
+    if (JOIN) atomicOr(reinterpret_cast<unsigned*>(mask) + (h >> 2), bit << (8 * (int)(h & 3)));
     else mask[h] = (unsigned char)bit;
   };
   inside::mark_cell(C.off + b3, sp, M.nv, M.tri, M.nt, o, G, [&](int x, int y, int z) { return site_of(L, x, y, z); },
@@ -56,14 +59,15 @@ hipError_t launch_mark_interior(const Cells& c, const Mesh& m, const Lattice& L,
                                 const unsigned char* cls, int n_class, int* flags, hipStream_t s) {
   if (c.n == 0) return hipSuccess;
   const size_t lds = (size_t)m.nv * 3 * sizeof(float);
-  auto go = [&](int only_class) {
-    hipLaunchKernelGGL(k_mark_interior, dim3(c.n), dim3(kMarkThreads), lds, s, c, m, L, mask, cls, only_class, flags);
+  auto go = [&](auto kern, int only_class) {
+    hipLaunchKernelGGL(kern, dim3(c.n), dim3(kMarkThreads), lds, s, c, m, L, mask, cls, only_class, flags);
     return hipGetLastError();
   };
-  if (!cls || c.n < kCellsPerClass * n_class) return go(-1);
+  if (!cls) return go(k_mark_interior<false>, -1);
+  if (c.n < kCellsPerClass * n_class) return go(k_mark_interior<true>, -1);
   // in increasing order, so that the highest class of a site is stored last
   for (int k = 0; k < n_class; ++k) {
-    const hipError_t e = go(k);
+    const hipError_t e = go(k_mark_interior<false>, k);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
