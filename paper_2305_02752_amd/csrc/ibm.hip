@@ -9,9 +9,10 @@
 //
 // Spreading and interpolation are organised by tile: one work-group per 8^3
 // tile walks the list of vertices whose stencil reaches the tile (built by
-// the binning kernels).  Spreading accumulates in LDS as 2^-40 fixed-point
-// int64 values; interpolation writes one partial sum per (vertex, tile) that
-// a per-vertex pass adds up in a fixed order.
+// the binning kernels).  Spreading accumulates in LDS in fixed point: int32 at
+// a scale of the tile, or int64 at 2^-40 with sheared images and in the reverse
+// sweep; interpolation writes one partial sum per (vertex, tile) that a
+// per-vertex pass adds up in a fixed order.
 // Integer addition is associative, so the result is bitwise independent of
 // the order in which waves and lanes arrive -- no global atomics, no
 // run-to-run drift.
@@ -369,6 +370,10 @@ __device__ __forceinline__ unsigned axis_run(int base, int n, int wall, int t0) 
   return c ? (unsigned)((lo - t0) | ((lo - p0) << 3) | (c << 5)) : 0u;
 }
 
+// The four weights of a fraction f from one hardware root.  Against 64 bits
+// over [0, 1): at most 4.5e-8, 0.8e-8 to 1.4e-8 rms; phi4's correctly rounded
+// root of a radicand with cancellation, once per weight: 7.0e-8, 1.5e-8 to
+// 1.9e-8 rms.
 template <int K>
 __device__ __forceinline__ void weights(float f, float (&W)[4]) {
   if (K == 4) {
@@ -749,7 +754,9 @@ __device__ __forceinline__ void interp(int m, const Lattice& L, const Smem<LE>& 
 // with it): writes body * g + the spread field, tile-major (padding slots
 // receive body * g).  Its entries are staged and sorted like the lattice
 // pass's, in int64 sums: one box of 32^3 14 us, 24.5 with a thread per unsorted
-// entry testing every node; 64 boxes of 48^3 53 and 61.
+// entry testing every node; 64 boxes of 48^3 53 and 61.  Its weights are
+// srt::weights, no further off than phi4's: p . dL/dp of 24 fits of one box
+// (sides 24 to 45, 40 or 60 steps) is on average 9.4e-7 off 64 bits with either.
 template <int K, class CT, class MT, class LT, class BT>
 __device__ __forceinline__ void spread_body(CT C, MT M, LT L, BT B, const float* __restrict__ vec, float body,
                                             float* __restrict__ F) {
